@@ -13,7 +13,7 @@ constexpr int MLP_HID = 64;      // hidden width
 constexpr int MLP_F = 64;        // subcarriers (outputs = 2 * MLP_F)
 
 struct MlpArgs {
-    const uint16_t *W2, *W3, *W2T, *W3T, *W1eT;
+    const uint16_t *W1, *W2, *W3;
     const float *b2, *b3;
     const float* Z1;
     const float* cb;
@@ -30,6 +30,7 @@ struct MlpArgs {
     const float* d_attr;
     float* clear;  // d_attr again when consumed rows are to be zeroed
     int64_t attr_stride;
+    bool wide;  // attribute rows are 16-byte aligned
     uint16_t *save_h1, *save_h2, *save_do, *save_dz2, *save_dz1;
     float *db3, *db2, *dc, *dE;
 };
