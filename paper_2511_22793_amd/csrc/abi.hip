@@ -137,7 +137,6 @@ gs_status check_forward(const gs_scene* sc, const gs_attrs* a, const gs_queries*
 void enqueue_prepare(const gs_scene* scene, const gs_queries* queries, const gs_grid* grid,
                             const gs_params* prm, const Layout& L, char* ws, hipStream_t s)
 {
-    launch_fill_u32((uint32_t*)(ws + L.flags), FL_WORDS, L.s_flags / 4, L.nq, 0u, s);
     launch_project(*scene, *queries, *grid, *prm, L, ws, s);
     launch_depth_sort(L, ws, s);
     launch_binning(L, ws, s);

@@ -378,11 +378,6 @@ constexpr int EMIT_RANKS = 64;
 // thousand blocks)
 constexpr int EMIT_SCAN_BLOCKS = 2048;
 
-__device__ __forceinline__ uint32_t ntiles_at(const uint32_t* order, const uint4* tinfo, uint32_t k, uint32_t nvis)
-{
-    return k < nvis ? tinfo[order[k]].w : 0u;
-}
-
 // Exclusive scan within a 256-thread workgroup; returns the prefix of v.
 __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_t* wsum)
 {
@@ -401,18 +396,36 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_
 }
 
 // Sum of the tile counts of each EMIT_RANKS block of the depth order (one
-// wave per block).
-__global__ __launch_bounds__(64) void k_scan_reduce(const uint32_t* __restrict__ order, size_t s_order,
+// wave per block).  Culled Gaussians sort to the end (key ~0), so the last
+// valid key's rank gives the visible count: its thread stores it.  The same
+// threads count the invalid inputs (rare: the atomic runs only for a wave
+// that has one).
+__global__ __launch_bounds__(64) void k_scan_reduce(const uint32_t* __restrict__ keys,
+                                                    const uint32_t* __restrict__ order, size_t s_order, uint32_t n,
                                                     const uint4* __restrict__ tinfo, size_t s_tinfo,
-                                                    const uint32_t* __restrict__ flags, size_t s_flags,
+                                                    const uint32_t* __restrict__ status, size_t s_status,
+                                                    uint32_t* __restrict__ flags, size_t s_flags,
                                                     uint32_t* __restrict__ partial, size_t s_partial)
 {
     const int q = blockIdx.y;
-    const uint32_t nvis = flags[q * s_flags + FL_NVIS];
     const uint32_t k = blockIdx.x * EMIT_RANKS + threadIdx.x;
-    uint32_t v = ntiles_at(order + q * s_order, tinfo + q * s_tinfo, k, nvis);
+    keys += q * s_order;
+    flags += q * s_flags;
+    uint32_t v = 0u;
+    bool bad = false;
+    if (k < n) {
+        bad = status[q * s_status + k] == ST_INVALID;
+        if (keys[k] != 0xFFFFFFFFu) {
+            v = tinfo[q * s_tinfo + order[q * s_order + k]].w;
+            if (k + 1 == n || keys[k + 1] == 0xFFFFFFFFu) flags[FL_NVIS] = k + 1;
+        }
+    }
+    const unsigned long long nb = __ballot(bad);
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (threadIdx.x == 0) partial[q * s_partial + blockIdx.x] = v;
+    if (threadIdx.x == 0) {
+        partial[q * s_partial + blockIdx.x] = v;
+        if (nb) atomicAdd(&flags[FL_INVALID], (uint32_t)__popcll(nb));
+    }
 }
 
 // Exclusive scan of the block sums; records the pair count and overflow.
@@ -562,8 +575,9 @@ void launch_binning(const Layout& L, char* ws, hipStream_t s)
     uint32_t* partial = (uint32_t*)(ws + L.partial);
     const size_t so = L.s_keys / 4, sti = L.s_tinfo / sizeof(uint4), sf = L.s_flags / 4, sp = L.s_partial / 4;
     const int nblk = (L.n + EMIT_RANKS - 1) / EMIT_RANKS;
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk, L.nq), dim3(64), 0, s, order, so, tinfo, sti, flags, sf,
-                       partial, sp);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk, L.nq), dim3(64), 0, s, (const uint32_t*)(ws + L.keys_a), order, so,
+                       (uint32_t)L.n, tinfo, sti, (const uint32_t*)(ws + L.status), L.s_status / 4, flags, sf, partial,
+                       sp);
     uint32_t* pa = (uint32_t*)(ws + L.pkeys_a);
     uint32_t* pb = (uint32_t*)(ws + L.pkeys_b);
     const size_t spk = L.s_pkeys / 4;
