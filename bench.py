@@ -267,7 +267,7 @@ def main():
                                                                                          FLOPS_BWD_CONTRIB)
         kt = {"k_train_fb + k_train_walk": (kernel_ms["train"], train_flops, "mfma", PEAK_MFMA_F32_TFLOPS)}
     else:
-        fwd_name = "k_blend<32, true>" if args.loss_mode == "fused" else "k_blend_sg<1>"
+        fwd_name = "k_blend<32, true>" if args.loss_mode == "fused" else "k_blend_mx<2, false>"
         bwd_name = "k_blend_bwd_sg<1, %s>" % ("true" if args.loss_mode == "target" else "false")
         kt = {fwd_name: (kernel_ms["blend"], blend_flops, "mfma", PEAK_MFMA_F32_TFLOPS),
               bwd_name: (kernel_ms["blend_bwd"], bwd_flops, "mfma", PEAK_MFMA_F32_TFLOPS)}

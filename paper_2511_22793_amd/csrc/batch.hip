@@ -63,13 +63,14 @@ static gs_status build_table(const gs_batch_job* jobs, int n_jobs, std::vector<B
         if (st != GS_OK) return st;
         const int C = b.attrs.is_complex ? 2 : 1;
         const int Fc = b.attrs.n_chan * C;
-        int cg = choose_chan_group(Fc, b.params.chan_group);
-        if (cg > 32) cg = 32;  // the persistent kernel carries groups up to 32
+        const int cg = choose_blend_group(Fc, b.params.chan_group);
         BlendJob J = make_blend_job(b.attrs, b.params, L, L.nq, (char*)b.workspace, b.spectrum);
         J.cg = cg;
-        J.ncg = Fc / cg;
+        J.ncg = (Fc + cg - 1) / cg;
         J.item_begin = (uint32_t)items;
         J.query0 = (int)nq_total;
+        blend_mx_form(&J, L.n);
+        if (cg > BLEND_ROW_CG) J.ncg = std::min(J.ncg, (Fc + 16 * J.nv - 1) / (16 * J.nv));
         items += (uint64_t)L.T * (uint64_t)J.ncg * (uint64_t)L.nq;
         nq_total += L.nq;
         if (items >= 0xFFFFFFFFull || nq_total > 0x7FFFFFFF) return GS_ERR_CAPACITY;

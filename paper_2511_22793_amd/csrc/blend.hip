@@ -1,26 +1,36 @@
 // Front-to-back compositing of the per-tile depth-ordered lists (Eq. (3),
 // Sec. 4.2; the per-pixel loop of Algorithm 1).  One workgroup per
-// (tile, channel group, query), one thread per pixel.  Batches of the
-// tile's list are staged in LDS; every thread walks the batch in order:
-//   dx, dy      pixel-centre offset, azimuth wrapped into [-W/2, W/2)  (FP64)
-//   q           conic quadratic form                                  (FP64)
-//   G           exp(-q/2) via v_exp_f32                               (FP32)
-//   alpha       min(alpha_max, opacity G); skip when alpha < alpha_min
-//   stop        before the Gaussian that would take T below T_min
-//   out_f      += T alpha a_i v_{i,f} for the group's channels        (FP32)
-// The whole workgroup leaves the list once every pixel has stopped.
-// The attribute row of the current Gaussian is wave-uniform and is read
-// through scalar loads.
+// (tile, channel group, query), one thread per pixel; its waves run on their
+// own (no workgroup barrier).  A wave takes the list 64 entries at a time:
+//   each lane tests one entry against the box of the wave's 64 pixels, the
+//   entries that reach it are queued in LDS in list order (the next 64
+//   records are already on their way), and the queue is walked four entries
+//   at a time: their
+//     dx, dy      pixel-centre offset, azimuth wrapped into [-W/2, W/2)  (FP64)
+//     q           conic quadratic form                                  (FP64)
+//     G           exp(-q/2) via v_exp_f32                               (FP32)
+//     alpha       min(alpha_max, opacity G)
+//   are independent of each other, only the short chain
+//     skip when alpha < alpha_min, stop below T_min, T, weight
+//   runs entry by entry, and
+//     out_f      += T alpha a_i v_{i,f} for the group's channels        (FP32)
+// What bounds it is that chain and the entries evaluated per wave.  A tile's
+// list holds every Gaussian whose rectangle touches the tile (thousands where
+// the view runs along a wall), most of which miss a given 64 pixels; one
+// entry at a time cost ~300 cycles of latency each.
+// One channel: 2048 Gaussians, one receiver 61 -> 26 us, 50k Gaussians, 16
+// receivers 245 -> 81 us, 300k Gaussians, one receiver 27 -> 11 us.
 #include <type_traits>
 
 #include "common.h"
+#include "walk.h"
 
 namespace gs {
 
-constexpr double LOG2E = 1.4426950408889634;
+constexpr double LOG2E = WALK_LOG2E;
 
 // Attribute rows are read-only for the whole launch: reading them through a
-// constant-address-space pointer lets the wave-uniform row go through the
+// constant-address-space pointer lets a wave-uniform row go through the
 // scalar cache (s_load) whatever the kernel stores elsewhere.
 typedef __attribute__((address_space(4))) const float CFloat;
 // The other buffers are global memory; naming the address space keeps the
@@ -28,34 +38,30 @@ typedef __attribute__((address_space(4))) const float CFloat;
 // instructions.
 #define GLOBAL_AS __attribute__((address_space(1)))
 
-// LDS batch of one tile's list (declared once per kernel, so that the
-// channel-group instantiations of one kernel share it).
-struct BlendLds {
-    double px[256], py[256], ca[256], cb[256], cc[256];
-    float sig[256], att[256];
-    uint32_t g[256];
-    // per wave: pixel weights of a run of 16 entries (matrix-core path), then
-    // the output transpose (64 pixels x 17)
-    float w[4][16][68];
+// LDS of one wave (declared once per kernel, so that the channel-group
+// instantiations of one kernel share it): the queue, and pixel weights of a
+// run of 16 entries (matrix-core path), the output transpose (64 pixels x
+// 17), or the queued entries' attribute values (up to 8 channels).
+
+struct alignas(16) BlendWave {
+    WalkQueue Q;
+    union {
+        float w[16][68];
+        float tr[64 * 17];
+        float v[WALK_BATCH][BLEND_ROW_CG];
+    } u;
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void wave_sync_lds()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+__device__ __forceinline__ void wave_sync_lds() { walk_wave_sync(); }
 
-// One (tile, channel group, set) of a blend job; every thread of the
-// workgroup must call it (it synchronises).  Threads beyond the tile's pixel
-// count idle.
+// One wave's part of one (tile, channel group, set) of a blend job.  A group
+// may reach past the last channel: those channels are zero and not stored.
 // The buffers are passed as restrict parameters so that, once inlined, the
-// attribute rows are known not to alias the stores and load through the
-// scalar cache.
+// attribute rows are known not to alias the stores.
 template <int CG, bool FUSE = false>
-__device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, int tile, int cg, int set,
+__device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW, int tile, int cg, int set,
                                                 const GRec* __restrict__ rec, const uint32_t* __restrict__ plist,
                                                 const uint2* __restrict__ ranges, const float* __restrict__ attr,
                                                 float* __restrict__ out, float* __restrict__ T_final,
@@ -64,38 +70,43 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
     const int q = J.shared_geo ? 0 : set;  // geometry query
     const int nthr = J.tw * J.th;
     const int txi = tile % J.TX, tyi = tile / J.TX;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lx = threadIdx.x % J.tw, ly = threadIdx.x / J.tw;
     const int col = txi * J.tw + lx, row = tyi * J.th + ly;
     const bool inside = (int)threadIdx.x < nthr && col < J.W && row < J.H;
+    WaveBox box;
+    const bool any = wave_box(wave, txi, tyi, J.tw, J.th, J.H, J.W, box);
+    if (!any && (!FUSE || wave >= (nthr >> 6))) return;
+    BlendWave& S = SW[wave];
     uint2 rg;
     {
         const unsigned long long r = ((const GLOBAL_AS unsigned long long*)ranges)[q * J.s_ranges + tile];
         rg.x = (uint32_t)r;
         rg.y = (uint32_t)(r >> 32);
     }
+    const uint32_t len = any ? rg.y - rg.x : 0u;
     const double pcx = col + 0.5, pcy = row + 0.5, halfW = 0.5 * J.W;
     const double Wd = (double)J.W;
     rec += q * J.s_rec;
-    plist += q * J.s_plist;
+    plist += q * J.s_plist + rg.x;
     const int Fc = J.Fc;
+    const int chn = min(CG, Fc - cg * CG);  // channels of this group
     const float* A = attr + set * J.a_stride + cg * CG;
     const float amin = J.amin, amax = J.amax, tmin = J.tmin;
 
-    float T = 1.0f;
-    uint32_t last = 0, cnt = 0;
-    bool done = !inside;
+    WalkState px{1.0f, inside ? amin : INFINITY, 0u, 0u};
     const size_t HW = (size_t)J.H * J.W, pix = inside ? (size_t)row * J.W + col : 0;
     const int cs = J.C - 1;  // C is 1 or 2
     const size_t obase = (size_t)set * Fc * HW;
-    // CG = 16, 32: the channel sums out[p][f] = sum_e w[p][e] v[e][f] of a
+    // CG = 16, 32, 64: the channel sums out[p][f] = sum_e w[p][e] v[e][f] of a
     // run of 16 entries go to the FP32 matrix cores (v_mfma_f32_16x16x4_f32,
     // A = the wave's pixel weights from LDS, B = the entries' attribute
-    // rows); the walk only produces the weights.  Smaller groups
-    // accumulate on the VALU with the row in SGPRs.
+    // rows); the walk only produces the weights.  Smaller groups accumulate
+    // on the VALU, the values queued with the entries.
     constexpr bool MF = CG == 16 || CG == 32 || CG == 64;
     constexpr int NB = MF ? CG / 16 : 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float acc[MF ? 1 : CG];
+    constexpr int VG = MF ? 1 : CG;
+    float acc[VG];
     f32x4 macc[MF ? 4 : 1][NB];
     if constexpr (MF) {
 #pragma unroll
@@ -107,104 +118,109 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
         for (int k = 0; k < CG; ++k) acc[k] = 0.0f;
     }
 
-    for (uint32_t b0 = rg.x; b0 < rg.y; b0 += nthr) {
-        if (__syncthreads_count(done) == (int)blockDim.x) break;
-        const uint32_t i = b0 + threadIdx.x;
-        if ((int)threadIdx.x < nthr && i < rg.y) {
-            const uint32_t g = ((const GLOBAL_AS uint32_t*)plist)[i];
-            const GLOBAL_AS GRec& r = ((const GLOBAL_AS GRec*)rec)[g];
-            S.px[threadIdx.x] = r.px;
-            S.py[threadIdx.x] = r.py;
-            S.ca[threadIdx.x] = r.ca;
-            S.cb[threadIdx.x] = r.cb;
-            S.cc[threadIdx.x] = r.cc;
-            S.sig[threadIdx.x] = r.sigma;
-            S.att[threadIdx.x] = r.att;
-            S.g[threadIdx.x] = g;
+    // the lane's entry of the batch ahead: its Gaussian, record and values,
+    // and the Gaussian of the batch after that
+    uint32_t g_next = 0u, g_after = 0u;
+    GRec r_next;
+    float v_next[VG];
+    auto fetch_g = [&](uint32_t b) -> uint32_t {
+        return b + lane < len ? ((const GLOBAL_AS uint32_t*)plist)[b + lane] : 0u;
+    };
+    auto fetch = [&]() {
+        const GLOBAL_AS GRec& r = ((const GLOBAL_AS GRec*)rec)[g_next];
+        r_next = GRec{r.px, r.py, r.ca, r.cb, r.cc, r.sigma, r.att};
+        if constexpr (!MF) {
+            const CFloat* vp = (const CFloat*)(A + (size_t)g_next * Fc);
+#pragma unroll
+            for (int k = 0; k < CG; ++k) v_next[k] = k < chn ? vp[k] : 0.0f;
         }
-        __syncthreads();
-        const int m = (int)min((uint32_t)nthr, rg.y - b0);
-        if constexpr (MF) {
-            for (int j0 = 0; j0 < m; j0 += 16) {
-                if (__ballot(!done) == 0ull) break;  // wave-uniform: all its pixels stopped
-                const int jn = min(16, m - j0);
-                // B operands of the run, loaded ahead of the walk: lane holds
-                // v[entry 4 ks + lane/16][channel 16 nb + lane%16]
-                float bv[4][NB];
+    };
+    if (len > 0) {
+        g_next = fetch_g(0);
+        g_after = fetch_g(WALK_BATCH);
+        fetch();
+    }
+    for (uint32_t b0 = 0; b0 < len; b0 += WALK_BATCH) {
+        int slot;
+        bool plain;
+        const int m = walk_queue(S.Q, r_next, g_next, b0 + lane + 1, b0 + lane < len, box, Wd, amin, lane, slot, plain);
+        if constexpr (!MF) {
+            const bool pad = lane >= m && lane < (m + WALK_STEP - 1) / WALK_STEP * WALK_STEP;
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const int e = 4 * ks + (lane >> 4);
-                    const bool ev = e < jn;
-                    const float* vr = A + (size_t)(ev ? S.g[j0 + e] : 0u) * Fc + (lane & 15);
+            for (int k = 0; k < CG; ++k) {
+                if (slot >= 0) S.u.v[slot][k] = v_next[k];
+                if (pad) S.u.v[lane][k] = 0.0f;
+            }
+        }
+        if (b0 + WALK_BATCH < len) {
+            g_next = g_after;
+            g_after = fetch_g(b0 + 2 * WALK_BATCH);
+            fetch();
+        }
+        wave_sync_lds();
+        auto walk = [&](auto pl) {
+            constexpr bool PLAIN = decltype(pl)::value;
+            if constexpr (MF) {
+                for (int j0 = 0; j0 < m; j0 += 16) {
+                    if (walk_done(px)) break;  // all the wave's pixels stopped
+                    // B operands of the run, loaded ahead of the walk: lane holds
+                    // v[entry 4 ks + lane/16][channel 16 nb + lane%16]
+                    float bv[4][NB];
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) bv[ks][nb] = ev ? ((const CFloat*)vr)[16 * nb] : 0.0f;
-                }
-#pragma unroll 4
-                for (int jj = 0; jj < 16; ++jj) {
-                    const int j = j0 + jj;
-                    float wgt = 0.0f;
-                    if (jj < jn && !done) {
-                        double dx = pcx - S.px[j];
-                        dx += dx >= halfW ? -Wd : (dx < -halfW ? Wd : 0.0);
-                        const double dy = pcy - S.py[j];
-                        const double qv = S.ca[j] * dx * dx + 2.0 * S.cb[j] * dx * dy + S.cc[j] * dy * dy;
-                        const float G = __builtin_amdgcn_exp2f((float)(-0.5 * LOG2E * qv));
-                        const float alpha = fminf(amax, S.sig[j] * G);
-                        const float Tn = T * (1.0f - alpha);
-                        const bool stop = alpha >= amin && Tn < tmin;
-                        const bool take = alpha >= amin && !stop;
-                        done = stop;
-                        wgt = take ? T * alpha * S.att[j] : 0.0f;
-                        T = take ? Tn : T;
-                        last = take ? b0 + j + 1 - rg.x : last;
-                        cnt += take ? 1u : 0u;
-                    }
-                    S.w[wave][jj][lane] = wgt;
-                }
-                wave_sync_lds();
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-#pragma unroll
-                    for (int pb = 0; pb < 4; ++pb) {
-                        const float a = S.w[wave][4 * ks + (lane >> 4)][16 * pb + (lane & 15)];
+                    for (int ks = 0; ks < 4; ++ks) {
+                        const int e = j0 + 4 * ks + (lane >> 4);
+                        const bool ev = e < m;
+                        const CFloat* vr = (const CFloat*)(A + (size_t)(ev ? S.Q.g[e] : 0u) * Fc + (lane & 15));
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb)
-                            macc[pb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[ks][nb], macc[pb][nb], 0, 0, 0);
+                            bv[ks][nb] = ev && 16 * nb + (lane & 15) < chn ? vr[16 * nb] : 0.0f;
                     }
+                    int steps = 0;  // K-steps whose weights are in LDS
+#pragma unroll 1
+                    for (int ks = 0; ks < 4; ++ks) {
+                        const int j = j0 + WALK_STEP * ks;
+                        if (j >= m || walk_done(px)) break;
+                        float w[WALK_STEP];
+                        walk_step<PLAIN>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
+#pragma unroll
+                        for (int i = 0; i < WALK_STEP; ++i) S.u.w[WALK_STEP * ks + i][lane] = w[i];
+                        steps = ks + 1;
+                    }
+                    wave_sync_lds();
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) {
+                        if (ks < steps) {
+#pragma unroll
+                            for (int pb = 0; pb < 4; ++pb) {
+                                const float a = S.u.w[4 * ks + (lane >> 4)][16 * pb + (lane & 15)];
+#pragma unroll
+                                for (int nb = 0; nb < NB; ++nb)
+                                    macc[pb][nb] =
+                                        __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[ks][nb], macc[pb][nb], 0, 0, 0);
+                            }
+                        }
+                    }
+                    wave_sync_lds();
                 }
-                wave_sync_lds();
-            }
-        } else {
-            for (int j = 0; j < m && !done; ++j) {
-                // the attribute row is wave-uniform: issue its scalar loads
-                // first so that the alpha evaluation below hides their latency
-                const uint32_t g = __builtin_amdgcn_readfirstlane(S.g[j]);
-                const CFloat* vp = (const CFloat*)(A + (size_t)g * Fc);
-                float v[CG];
+            } else {
+#pragma unroll 1
+                for (int j = 0; j < m; j += WALK_STEP) {
+                    if (walk_done(px)) break;
+                    float w[WALK_STEP];
+                    walk_step<PLAIN>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
 #pragma unroll
-                for (int k = 0; k < CG; ++k) v[k] = vp[k];
-                double dx = pcx - S.px[j];
-                dx += dx >= halfW ? -Wd : (dx < -halfW ? Wd : 0.0);
-                const double dy = pcy - S.py[j];
-                const double qv = S.ca[j] * dx * dx + 2.0 * S.cb[j] * dx * dy + S.cc[j] * dy * dy;
-                const float G = __builtin_amdgcn_exp2f((float)(-0.5 * LOG2E * qv));
-                const float alpha = fminf(amax, S.sig[j] * G);
-                const float Tn = T * (1.0f - alpha);
-                const bool stop = alpha >= amin && Tn < tmin;
-                const bool take = alpha >= amin && !stop;
-                done = stop;
-                // branch-free update (one basic block, so the row loads issue
-                // first): a skipped pair adds zero and keeps T
-                const float wgt = take ? T * alpha * S.att[j] : 0.0f;
+                    for (int i = 0; i < WALK_STEP; ++i)
 #pragma unroll
-                for (int k = 0; k < CG; ++k) acc[k] = fmaf(wgt, v[k], acc[k]);
-                T = take ? Tn : T;
-                last = take ? b0 + j + 1 - rg.x : last;
-                cnt += take ? 1u : 0u;
+                        for (int k = 0; k < CG; ++k) acc[k] = fmaf(w[i], S.u.v[j + i][k], acc[k]);
+                }
             }
-        }
+        };
+        if (plain) walk(std::true_type{});
+        else walk(std::false_type{});
+        if (walk_done(px)) break;
+        wave_sync_lds();  // the next batch reuses the queue
     }
-    __syncthreads();  // the LDS batch may be reused by the caller's next item
+    wave_sync_lds();  // the transpose, and the caller's next item, reuse the LDS
     // the fused loss (FUSE: k_blend with a target): per written element the
     // target, the elementwise gradient part and the three sums,
     // reduce-scattered over the wave (lane 4 k + 0 ends with channel k's
@@ -216,8 +232,8 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
         constexpr int V = decltype(vc)::value;
         wave_reduce_scatter<V>(x, lane);
         constexpr int sh = V >= 64 ? 0 : (V == 32 ? 1 : (V == 16 ? 2 : (V == 8 ? 3 : (V == 4 ? 4 : (V == 2 ? 5 : 6)))));
-        if ((lane & ((1 << sh) - 1)) == 0) {
-            const int ch = ch0 + (lane >> sh);
+        const int ch = ch0 + (lane >> sh);
+        if ((lane & ((1 << sh) - 1)) == 0 && ch < Fc) {
             J.lpart[(((size_t)set * Fc + ch) * 3 + slot) * J.lnp + (size_t)tile * (nthr >> 6) + wave] = x[0];
         }
     };
@@ -226,7 +242,7 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
         // transpose through LDS so that each lane writes its own pixel
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            float* tr = &S.w[wave][0][0];  // [64 pixels][17]
+            float* tr = S.u.tr;  // [64 pixels][17]
 #pragma unroll
             for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
@@ -241,12 +257,12 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
                 float x[16], y[16];
 #pragma unroll
                 for (int k = 0; k < 16; ++k)
-                    y[k] = inside ? J.tgt[obase + spec_offset(ch0 + k, pix, cs, HW)] : 0.0f;
+                    y[k] = inside && ch0 + k < Fc ? J.tgt[obase + spec_offset(ch0 + k, pix, cs, HW)] : 0.0f;
 #pragma unroll
                 for (int k = 0; k < 16; ++k) {
                     const size_t idx = obase + spec_offset(ch0 + k, pix, cs, HW);
                     const float o = tr[lane * 17 + k];
-                    if (inside) {
+                    if (inside && ch0 + k < Fc) {
                         ((GLOBAL_AS float*)out)[idx] = o;
                         if (J.dpart) J.dpart[idx] = J.lscale * (o - y[k]);
                     }
@@ -264,7 +280,7 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
 #pragma unroll
                 for (int k = 0; k < 16; ++k) {
                     const int ch = cg * CG + 16 * nb + k;
-                    ((GLOBAL_AS float*)out)[obase + spec_offset(ch, pix, cs, HW)] = tr[lane * 17 + k];
+                    if (ch < Fc) ((GLOBAL_AS float*)out)[obase + spec_offset(ch, pix, cs, HW)] = tr[lane * 17 + k];
                 }
             }
             wave_sync_lds();
@@ -273,11 +289,12 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
         if constexpr (fuse) {
             float x[CG], y[CG];
 #pragma unroll
-            for (int k = 0; k < CG; ++k) y[k] = inside ? J.tgt[obase + spec_offset(cg * CG + k, pix, cs, HW)] : 0.0f;
+            for (int k = 0; k < CG; ++k)
+                y[k] = inside && k < chn ? J.tgt[obase + spec_offset(cg * CG + k, pix, cs, HW)] : 0.0f;
 #pragma unroll
             for (int k = 0; k < CG; ++k) {
                 const size_t idx = obase + spec_offset(cg * CG + k, pix, cs, HW);
-                if (inside) {
+                if (inside && k < chn) {
                     ((GLOBAL_AS float*)out)[idx] = acc[k];
                     if (J.dpart) J.dpart[idx] = J.lscale * (acc[k] - y[k]);
                 }
@@ -296,80 +313,459 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendLds& S, 
 #pragma unroll
             for (int k = 0; k < CG; ++k) {
                 const int ch = cg * CG + k;
-                ((GLOBAL_AS float*)out)[obase + spec_offset(ch, pix, cs, HW)] = acc[k];
+                if (k < chn) ((GLOBAL_AS float*)out)[obase + spec_offset(ch, pix, cs, HW)] = acc[k];
             }
         }
     }
     if (cg == 0 && set == q && T_final) {
-        ((GLOBAL_AS float*)T_final)[q * J.s_pix + pix] = T;
-        ((GLOBAL_AS uint32_t*)n_last)[q * J.s_pix + pix] = last;
-        ((GLOBAL_AS uint32_t*)n_contrib)[q * J.s_pix + pix] = cnt;
+        ((GLOBAL_AS float*)T_final)[q * J.s_pix + pix] = px.T;
+        ((GLOBAL_AS uint32_t*)n_last)[q * J.s_pix + pix] = px.last;
+        ((GLOBAL_AS uint32_t*)n_contrib)[q * J.s_pix + pix] = px.cnt;
     }
 }
 
 template <int CG>
-__device__ __forceinline__ void blend_tile(const BlendJob& J, BlendLds& S, int tile, int cg, int set)
+__device__ __forceinline__ void blend_tile(const BlendJob& J, BlendWave* S, int tile, int cg, int set)
 {
     blend_tile_impl<CG>(J, S, tile, cg, set, J.rec, J.plist, J.ranges, J.attr, J.out, J.T_final, J.n_last,
                         J.n_contrib);
 }
 
+// waves per SIMD the registers are sized for: the four records in flight and
+// the accumulators of the matrix-core groups
+__host__ __device__ constexpr int blend_waves(int cg) { return cg >= 32 ? 2 : (cg >= 16 ? 3 : 4); }
+
 template <int CG, bool FUSE>
-__global__ __launch_bounds__(256) void k_blend(BlendJob J, const GRec* __restrict__ rec,
+__global__ __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(blend_waves(CG), blend_waves(CG)))) void k_blend(BlendJob J, const GRec* __restrict__ rec,
                                                const uint32_t* __restrict__ plist, const uint2* __restrict__ ranges,
                                                const float* __restrict__ attr, float* __restrict__ out,
                                                float* __restrict__ T_final, uint32_t* __restrict__ n_last,
                                                uint32_t* __restrict__ n_contrib)
 {
-    __shared__ BlendLds S;
+    __shared__ BlendWave S[4];
     blend_tile_impl<CG, FUSE>(J, S, blockIdx.x, blockIdx.y, blockIdx.z, rec, plist, ranges, attr, out, T_final,
                               n_last, n_contrib);
 }
 
+// ---------------------------------------------------------------------------
+// Compositing of many channels: the weights w_k(p) = T_k alpha_k a_k do not
+// depend on the channel (nor, over one shared geometry, on the attribute
+// set), so for every column c = (set, channel component) of the spectrum
+//   out(p, c) = sum_k w_k(p) v(k, c)
+// is one product of the weights (entries x pixels) with the attribute rows
+// (entries x columns).  A wave owns 64 pixels of a tile (the tile's in-image
+// pixels packed into groups of 64) and a range of column blocks.  It walks
+// the list until MX_STEPS steps of 4 entries that weigh anywhere are buffered
+// in LDS or the walk ends, takes the weights into registers as matrix-core
+// operands (v_mfma_f32_16x16x4_f32, B = entries x pixels), and then its column
+// blocks (A = columns x entries); a lane ends with neighbouring columns of
+// one pixel and stores them.  A walk longer than the buffer starts the next
+// products from the stored sums, so every sum is one chain of fused
+// multiply-adds in list order however it is cut (and is what k_blend forms
+// one entry at a time).
+// Bound: matrix cores (32 cycles per 4 entries x 16 pixels x 16 columns) and
+// the spectrum's stores (non-temporal: cached ones left the L2 as half
+// lines).
+// 64 sets of 128 columns at 100k Gaussians, 90 x 360 (1.06 GB stored): 614 us
+// with one wave of eight walking while the others wait, 349 now (391 with
+// cached stores); 4 receivers of 32 columns at 20k Gaussians: 555 us with the
+// list walked one entry at a time, 75 now.
+// ---------------------------------------------------------------------------
+constexpr int MX_WIDE = 2;
+constexpr int MX_STEPS = 16;
+constexpr int MX_ROWS = WALK_STEP * MX_STEPS;
+constexpr uint32_t MX_OOB = 0x80000000u;  // past mx_rsrc's range
+constexpr int MX_NT = 2;                  // non-temporal: the spectrum is not read again here
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t mx_rsrc(const void* base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7FFFFFFF, 0x00020000);
+}
+// LDS of one wave: the queue, the buffered weights (pixel p at column
+// 4 (p % 16) + p / 16, so that a lane's operands of one step are one 16-byte
+// read) and the Gaussians of the buffered entries.
+struct alignas(16) MxWave {
+    WalkQueue Q;
+    float w[MX_ROWS][64];
+    uint32_t g[MX_ROWS];
+};
+
+// What the products of one group need besides the buffered weights.
+struct MxOut {
+    const float* attr;
+    float* out;
+    int64_t a_stride;
+    size_t HW;
+    int Fc, cs, nbs;  // channel floats, log2 of the components, blocks per set
+    bool across;
+    int set, k0, kn, vw, x0, y0, W;
+    __device__ __forceinline__ int pixel(int k) const
+    {
+        return k < kn ? (y0 + k / vw) * W + x0 + k % vw : -1;
+    }
+    // block cb: its set and first column
+    __device__ __forceinline__ int block(int cb, int width, int& c0) const
+    {
+        const int s = across ? cb / nbs : set;
+        c0 = (across ? cb - s * nbs : cb) * width;
+        return s;
+    }
+};
+
+// out (+)= W^T V over NS steps for the column blocks [cb_lo, cb_hi), a set's
+// attributes and spectrum addressed by 32-bit byte offsets (the launcher has
+// checked that they fit and are aligned): accesses past the last column or
+// outside the image, and the rows past the buffered steps, go past the
+// buffers' range (reads give 0).  NV = 2: complex columns, 32 a block.
+// Loads wait in issue order behind the stores before them, so a block's are
+// issued ahead of the previous block's stores.
+template <int NV, int NS>
+__device__ __forceinline__ void mx_products(const MxOut& O, const MxWave& S, int steps, bool stored, int cb_lo, int cb_hi)
+{
+    const int lane = threadIdx.x & 63, j4 = lane >> 4, l16 = lane & 15;
+    const uint32_t HW4 = (uint32_t)O.HW * 4u;  // bytes of a column's plane (of a pair's: 2 HW4)
+    float wB[NS][4];                           // weight of entry 4 ks + j4 at pixel 16 pb + l16
+    uint32_t row[NS];                          // byte offset of entry 4 ks + j4's columns
+#pragma unroll
+    for (int ks = 0; ks < NS; ++ks) {
+        const float4 v = *(const float4*)&S.w[WALK_STEP * ks + j4][4 * l16];
+        wB[ks][0] = v.x;
+        wB[ks][1] = v.y;
+        wB[ks][2] = v.z;
+        wB[ks][3] = v.w;
+        const uint32_t g = S.g[WALK_STEP * ks + j4];
+        row[ks] = ks < steps ? (g * (uint32_t)O.Fc + NV * l16) * 4u : MX_OOB;
+    }
+    uint32_t so[4];  // byte offset of the lane's first column at pixel 16 pb + l16
+#pragma unroll
+    for (int pb = 0; pb < 4; ++pb) {
+        const int px = O.pixel(O.k0 + 16 * pb + l16);
+        so[pb] = px >= 0 ? 4u * NV * j4 * HW4 + ((uint32_t)px << O.cs) * 4u : MX_OOB;
+    }
+    float av[NS][NV];  // column NV l16 + v of entry 4 ks + j4
+    auto load = [&](int cb) {
+        int c0;
+        const int s = O.block(cb, 16 * NV, c0);
+        const __amdgpu_buffer_rsrc_t r = mx_rsrc(O.attr + s * O.a_stride + c0);
+        const uint32_t past = NV > 1 || c0 + l16 < O.Fc ? 0u : MX_OOB;
+#pragma unroll
+        for (int ks = 0; ks < NS; ++ks) {
+            if constexpr (NV == 1) {
+                av[ks][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, row[ks] | past, 0, 0));
+            } else {
+                const auto x = __builtin_amdgcn_raw_buffer_load_b64(r, row[ks], 0, 0);
+                __builtin_memcpy(av[ks], &x, 8);
+            }
+        }
+    };
+    load(cb_lo);
+#pragma unroll 1
+    for (int cb = cb_lo; cb < cb_hi; ++cb) {
+        int c0;
+        const int s = O.block(cb, 16 * NV, c0);
+        float* ob = O.out + ((size_t)s * O.Fc + c0) * O.HW;
+        const __amdgpu_buffer_rsrc_t r = mx_rsrc(ob);
+        // acc[v][pb][i]: column c0 + NV (4 j4 + i) + v of pixel 16 pb + l16
+        f32x4 acc[NV][4];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int pb = 0; pb < 4; ++pb) acc[v][pb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        // byte offset of the lane's column offset e (of 4 NV) at pixel block pb
+        auto at = [&](int e, int pb) -> uint32_t {
+            const uint32_t past = NV > 1 || c0 + 4 * j4 + e < O.Fc ? 0u : MX_OOB;
+            const uint32_t plane = O.cs ? (uint32_t)(e & ~1) * HW4 + (e & 1) * 4u : e * HW4;
+            return (so[pb] + plane) | past | (so[pb] & MX_OOB);
+        };
+        if (stored) {
+#pragma unroll
+            for (int e = 0; e < 4 * NV; ++e)
+#pragma unroll
+                for (int pb = 0; pb < 4; ++pb)
+                    acc[e % NV][pb][e / NV] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at(e, pb), 0, 0));
+        }
+#pragma unroll
+        for (int ks = 0; ks < NS; ++ks)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int pb = 0; pb < 4; ++pb)
+                    acc[v][pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][v], wB[ks][pb], acc[v][pb], 0, 0, 0);
+        if (cb + 1 < cb_hi) load(cb + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        // the value of column offset e, in column order
+        auto val = [&](int pb, int e) { return __float_as_uint(acc[e % NV][pb][e / NV]); };
+        if (NV > 1 || O.cs) {
+#pragma unroll
+            for (int e = 0; e < 4 * NV; e += 2)
+#pragma unroll
+                for (int pb = 0; pb < 4; ++pb) {
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{val(pb, e), val(pb, e + 1)}, r, at(e, pb), 0, MX_NT);
+                }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4 * NV; ++e)
+#pragma unroll
+                for (int pb = 0; pb < 4; ++pb) __builtin_amdgcn_raw_buffer_store_b32(val(pb, e), r, at(e, pb), 0, MX_NT);
+        }
+    }
+}
+
+// The same in 64-bit addressing, for attributes or spectra past 2 GiB a set
+// and for complex spectra that are not 8-byte aligned.
+__device__ __forceinline__ void mx_products_big(const MxOut& O, const MxWave& S, int steps, bool stored, int cb_lo,
+                                                int cb_hi)
+{
+    const int lane = threadIdx.x & 63, j4 = lane >> 4, l16 = lane & 15;
+#pragma unroll 1
+    for (int cb = cb_lo; cb < cb_hi; ++cb) {
+        int c0;
+        const int s = O.block(cb, 16, c0);
+        const CFloat* vb = (const CFloat*)(O.attr + s * O.a_stride + c0 + l16);
+        float* ob = O.out + (size_t)s * O.Fc * O.HW;
+        const int c = c0 + 4 * j4;
+        f32x4 acc[4];
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb) {
+            const int px = O.pixel(O.k0 + 16 * pb + l16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[pb][i] = stored && px >= 0 && c + i < O.Fc
+                                 ? ((const GLOBAL_AS float*)ob)[spec_offset(c + i, px, O.cs, O.HW)]
+                                 : 0.0f;
+        }
+#pragma unroll 1
+        for (int ks = 0; ks < steps; ++ks) {
+            const float a = c0 + l16 < O.Fc ? vb[(size_t)S.g[WALK_STEP * ks + j4] * O.Fc] : 0.0f;
+            const float4 w = *(const float4*)&S.w[WALK_STEP * ks + j4][4 * l16];
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w.x, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w.y, acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w.z, acc[2], 0, 0, 0);
+            acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w.w, acc[3], 0, 0, 0);
+        }
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb) {
+            const int px = O.pixel(O.k0 + 16 * pb + l16);
+            if (px < 0) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (c + i < O.Fc) ((GLOBAL_AS float*)ob)[spec_offset(c + i, px, O.cs, O.HW)] = acc[pb][i];
+        }
+    }
+}
+
+// Column blocks [cb_lo, cb_hi) of group pg of `tile`, 16 NV columns each (a
+// lane loads NV neighbouring columns of an entry); with J.across the blocks
+// run over the sets too (block = set * blocks per set + block), otherwise
+// they are those of `set`.  state: this unit stores the per-pixel walk state.
+// BIG: attributes and spectrum addressed in 64 bits (NV = 1).
+template <int NV, bool BIG>
+__device__ __forceinline__ void blend_mx_unit(const BlendJob& J, MxWave& S, int tile, int pg, int set, int cb_lo,
+                                              int cb_hi, bool state, const GRec* __restrict__ rec,
+                                              const uint32_t* __restrict__ plist, const uint2* __restrict__ ranges,
+                                              const float* __restrict__ attr, float* __restrict__ out,
+                                              float* __restrict__ T_final, uint32_t* __restrict__ n_last,
+                                              uint32_t* __restrict__ n_contrib, int min_walk)
+{
+    const int q = J.shared_geo ? 0 : set;  // geometry query
+    const int lane = threadIdx.x & 63, j4 = lane >> 4, l16 = lane & 15;
+    const int txi = tile % J.TX, tyi = tile / J.TX;
+    const int vw = min(J.tw, J.W - txi * J.tw), vh = min(J.th, J.H - tyi * J.th);
+    const int k0 = 64 * pg, kn = min(vw * vh, k0 + 64);  // the group's pixels of the tile
+    if (k0 >= kn) return;
+    auto pixel = [&](int k) { return k < kn ? (tyi * J.th + k / vw) * J.W + txi * J.tw + k % vw : -1; };
+    const int mypix = pixel(k0 + lane);
+    if (min_walk > 0) {
+        int m = mypix >= 0 ? (int)((const GLOBAL_AS uint32_t*)n_last)[mypix] : 0;
+        for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+        if (m <= min_walk) return;
+    }
+    uint2 rg;
+    {
+        const unsigned long long r = ((const GLOBAL_AS unsigned long long*)ranges)[q * J.s_ranges + tile];
+        rg.x = (uint32_t)r;
+        rg.y = (uint32_t)(r >> 32);
+    }
+    const uint32_t len = rg.y - rg.x;
+    rec += q * J.s_rec;
+    plist += q * J.s_plist + rg.x;
+    const double pcx = (mypix >= 0 ? mypix % J.W : 0) + 0.5, pcy = (mypix >= 0 ? mypix / J.W : 0) + 0.5;
+    const double halfW = 0.5 * J.W, Wd = (double)J.W;
+    const int y0 = k0 / vw, y1 = (kn - 1) / vw;  // a group of several rows spans the tile's columns
+    const WaveBox box{txi * J.tw + (y0 == y1 ? k0 % vw : 0) + 0.5, txi * J.tw + (y0 == y1 ? (kn - 1) % vw : vw - 1) + 0.5,
+                      tyi * J.th + y0 + 0.5, tyi * J.th + y1 + 0.5};
+    const float amin = J.amin, amax = J.amax, tmin = J.tmin;
+    const int Fc = J.Fc, cs = J.C - 1;
+    const size_t HW = (size_t)J.H * J.W;
+    const int nbs = (Fc + 16 * NV - 1) / (16 * NV);  // blocks per set
+
+    WalkState px{1.0f, mypix >= 0 ? amin : INFINITY, 0u, 0u};
+    int steps = 0;  // buffered steps
+    // the lane's Gaussian of the batch ahead
+    auto fetch_g = [&](uint32_t b) -> uint32_t {
+        return b + lane < len ? ((const GLOBAL_AS uint32_t*)plist)[b + lane] : 0u;
+    };
+    uint32_t g_next = fetch_g(0);
+    uint32_t b0 = 0;  // first list position not queued yet
+    int j = 0, m = 0;
+    bool plain = true, end = len == 0, stored = false;
+    for (;;) {
+        // fill the buffer
+        while (!end && steps < MX_STEPS) {
+            if (j >= m) {
+                if (b0 >= len) {
+                    end = true;
+                    break;
+                }
+                int slot;
+                const uint32_t g = g_next;
+                const GLOBAL_AS GRec& r = ((const GLOBAL_AS GRec*)rec)[g];
+                const GRec rr{r.px, r.py, r.ca, r.cb, r.cc, r.sigma, r.att};
+                g_next = fetch_g(b0 + WALK_BATCH);
+                wave_sync_lds();
+                m = walk_queue(S.Q, rr, g, b0 + lane + 1, b0 + lane < len, box, Wd, amin, lane, slot, plain);
+                b0 += WALK_BATCH;
+                wave_sync_lds();
+                j = 0;
+                continue;
+            }
+            float w[WALK_STEP];
+            if (plain) walk_step<true>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
+            else walk_step<false>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
+            if (__ballot(w[0] != 0.0f || w[1] != 0.0f || w[2] != 0.0f || w[3] != 0.0f) != 0ull) {
+#pragma unroll
+                for (int i = 0; i < WALK_STEP; ++i) S.w[WALK_STEP * steps + i][4 * l16 + j4] = w[i];
+                if (lane < WALK_STEP) S.g[WALK_STEP * steps + lane] = S.Q.g[j + lane];
+                ++steps;
+            }
+            j += WALK_STEP;
+            if (walk_done(px)) end = true;
+        }
+        // the products over the buffered entries, rounded up to a multiple of
+        // 4 steps with zero weights (the step count is a constant of each
+        // form: a branch per step would wait for every load one by one)
+        const int ns = steps <= 4 ? 4 : (steps + 3) & ~3;
+        for (int r = WALK_STEP * steps; r < WALK_STEP * ns; ++r) S.w[r][lane] = 0.0f;
+        wave_sync_lds();
+        const MxOut O{attr, out, J.a_stride, HW, Fc, cs, nbs, J.across != 0, set, k0, kn, vw, txi * J.tw, tyi * J.th, J.W};
+        if constexpr (BIG) {
+            mx_products_big(O, S, steps, stored, cb_lo, cb_hi);
+        } else {
+            if (ns == 4) mx_products<NV, 4>(O, S, steps, stored, cb_lo, cb_hi);
+            else if (ns == 8) mx_products<NV, 8>(O, S, steps, stored, cb_lo, cb_hi);
+            else if (ns == 12) mx_products<NV, 12>(O, S, steps, stored, cb_lo, cb_hi);
+            else mx_products<NV, 16>(O, S, steps, stored, cb_lo, cb_hi);
+        }
+        stored = true;
+        steps = 0;
+        wave_sync_lds();
+        if (end) break;
+    }
+    if (state && mypix >= 0 && T_final) {
+        ((GLOBAL_AS float*)T_final)[q * J.s_pix + mypix] = px.T;
+        ((GLOBAL_AS uint32_t*)n_last)[q * J.s_pix + mypix] = px.last;
+        ((GLOBAL_AS uint32_t*)n_contrib)[q * J.s_pix + mypix] = px.cnt;
+    }
+}
+
+// blockIdx.x = tile * J.ncg + column range (the ranges of a tile on
+// neighbouring workgroups, so on different XCDs, each of which
+// then reads its own columns of the attribute rows), blockIdx.z = set where
+// the sets have their own geometry.
+template <int NV, bool BIG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_blend_mx(
+    BlendJob J, const GRec* __restrict__ rec, const uint32_t* __restrict__ plist, const uint2* __restrict__ ranges,
+    const float* __restrict__ attr, float* __restrict__ out, float* __restrict__ T_final,
+    uint32_t* __restrict__ n_last, uint32_t* __restrict__ n_contrib, int min_walk)
+{
+    __shared__ MxWave S[4];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = blockIdx.x / J.ncg, cg = blockIdx.x % J.ncg, set = blockIdx.z;
+    const int nb = (J.Fc + 16 * NV - 1) / (16 * NV) * (J.across ? J.nsets : 1);
+    const int cb_lo = (int)((int64_t)cg * nb / J.ncg), cb_hi = (int)((int64_t)(cg + 1) * nb / J.ncg);
+    blend_mx_unit<NV, BIG>(J, S[wave], tile, wave, set, cb_lo, cb_hi, cg == 0 && set == (J.shared_geo ? 0 : set), rec,
+                           plist, ranges, attr, out, T_final, n_last, n_contrib, min_walk);
+}
+
 // Persistent blend over a table of jobs (scenes of any size, grid, tile
 // shape and channel count): each workgroup takes (job, tile, channel group,
-// set) items from a device counter until none are left -- every workgroup
-// exits once the counter passes the total -- and stamps the completion time
-// of the item's query.  Items are numbered job by job, then set by set, then
-// channel group, then tile, so a query's items are contiguous and the job
-// order is the service order.
-__global__ __launch_bounds__(256) void k_blend_persist(const BlendJob* __restrict__ jobs, int njobs, uint32_t total,
-                                                       uint32_t* counter, unsigned long long* done_ts)
+// set) items and stamps the completion time of the item's query.  Items are
+// numbered job by job, then set by set, then channel group, then tile, so a
+// query's items are contiguous and the job order is the service order.  The
+// first part of the items is dealt out in turn (item k to workgroup k mod
+// the grid); only the last quarter comes from a device counter, one item
+// ahead of its use: an atomic per item on one counter, ~13 ns each and one
+// after the other, bounded the launch (96 receivers over 8 scenes, 72k items: 2.11 ms; with the items dealt
+// out and the matrix-core form's single walk per tile 1.40 ms).
+// Every workgroup exits once its dealt items are done and the counter passes
+// the total.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_blend_persist(
+    const BlendJob* __restrict__ jobs, int njobs, uint32_t total, uint32_t* counter, unsigned long long* done_ts)
 {
-    __shared__ BlendLds S;
-    __shared__ uint32_t s_item;
-    __shared__ int s_job;
-    for (;;) {
-        if (threadIdx.x == 0) {
-            const uint32_t item = atomicAdd(counter, 1u);
-            int lo = 0, hi = njobs - 1;  // last job with item_begin <= item
+    __shared__ union PersistLds {
+        BlendWave v[4];
+        MxWave m[4];
+    } S;
+    __shared__ uint32_t s_item[2];
+    const int lane = threadIdx.x & 63;
+    const uint32_t rounds = (total - total / 4) / gridDim.x, dealt = rounds * gridDim.x;
+    const uint32_t first = lane < njobs ? jobs[lane].item_begin : 0xFFFFFFFFu;
+    for (uint32_t k = 0;; ++k) {
+        // the item after the dealt ones, one ahead
+        uint32_t ahead = 0u;
+        if (threadIdx.x == 0 && k + 1 >= rounds) ahead = dealt + atomicAdd(counter, 1u);
+        uint32_t item = k * gridDim.x + blockIdx.x;
+        if (k >= rounds) {
+            if (k == 0) {  // nothing was dealt: the first item is not known yet
+                if (threadIdx.x == 0) {
+                    s_item[1] = ahead;
+                    ahead = dealt + atomicAdd(counter, 1u);
+                }
+                __syncthreads();
+            }
+            item = s_item[(k + 1) & 1];
+        }
+        item = __builtin_amdgcn_readfirstlane(item);
+        if (item >= total) break;
+        int j = __popcll(__ballot(first <= item)) - 1;  // last job with item_begin <= item
+        if (njobs > 64) {
+            int lo = 0, hi = njobs - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
                 if (jobs[mid].item_begin <= item) lo = mid;
                 else hi = mid - 1;
             }
-            s_item = item;
-            s_job = lo;
+            j = lo;
         }
-        __syncthreads();
-        const uint32_t item = __builtin_amdgcn_readfirstlane(s_item);
-        const int j = __builtin_amdgcn_readfirstlane(s_job);
-        __syncthreads();
-        if (item >= total) break;
         const BlendJob& J = jobs[j];
         const uint32_t local = item - J.item_begin;
         const int tile = (int)(local % (uint32_t)J.T);
         const uint32_t rest = local / (uint32_t)J.T;
         const int cg = (int)(rest % (uint32_t)J.ncg);
         const int set = (int)(rest / (uint32_t)J.ncg);
-        switch (J.cg) {
-            case 1: blend_tile<1>(J, S, tile, cg, set); break;
-            case 2: blend_tile<2>(J, S, tile, cg, set); break;
-            case 4: blend_tile<4>(J, S, tile, cg, set); break;
-            case 8: blend_tile<8>(J, S, tile, cg, set); break;
-            case 16: blend_tile<16>(J, S, tile, cg, set); break;
-            default: blend_tile<32>(J, S, tile, cg, set); break;
+        if (J.cg > BLEND_ROW_CG) {
+            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            const int nb = (J.Fc + 16 * J.nv - 1) / (16 * J.nv);
+            const int cb_lo = cg * nb / J.ncg, cb_hi = (cg + 1) * nb / J.ncg;
+#define MX_ARGS J, S.m[wave], tile, wave, set, cb_lo, cb_hi, cg == 0, J.rec, J.plist, J.ranges, J.attr, J.out, J.T_final, \
+                J.n_last, J.n_contrib, 0
+            if (J.big) blend_mx_unit<1, true>(MX_ARGS);
+            else if (J.nv > 1) blend_mx_unit<MX_WIDE, false>(MX_ARGS);
+            else blend_mx_unit<1, false>(MX_ARGS);
+#undef MX_ARGS
+        } else {
+            switch (J.cg) {
+                case 1: blend_tile<1>(J, S.v, tile, cg, set); break;
+                case 2: blend_tile<2>(J, S.v, tile, cg, set); break;
+                case 4: blend_tile<4>(J, S.v, tile, cg, set); break;
+                default: blend_tile<8>(J, S.v, tile, cg, set); break;
+            }
         }
+        // the next item's index (two slots: a wave may still read the other),
+        // and every wave's part of this item is done
+        if (threadIdx.x == 0) s_item[k & 1] = ahead;
+        __syncthreads();
         if (threadIdx.x == 0 && done_ts) atomicMax(&done_ts[J.query0 + set], (unsigned long long)wall_clock64());
     }
 }
@@ -539,6 +935,7 @@ BlendJob make_blend_job(const gs_attrs& a, const gs_params& p, const Layout& L, 
     J.T = L.T;
     J.nsets = n_sets;
     J.shared_geo = (L.nq == 1 && n_sets > 1) ? 1 : 0;
+    J.across = 0;
     J.amin = p.alpha_min;
     J.amax = p.alpha_max;
     J.tmin = p.T_min;
@@ -555,223 +952,6 @@ BlendJob make_blend_job(const gs_attrs& a, const gs_params& p, const Layout& L, 
     return J;
 }
 
-// ---------------------------------------------------------------------------
-// Compositing of S attribute sets over one shared geometry (the training
-// batch: one receiver, S transmitters whose effect is in the attributes).
-// The pixel weight w_k(p) = T_k alpha_k a_k and the walk's decisions do not
-// depend on the set, so out[s][f](p) = sum_k w_k(p) v[s][k][f] is one
-// product of the weights W (entries x pixels) with the attribute rows V
-// (entries x S*F*c columns).  One workgroup (8 waves) takes 64 pixels of a
-// tile (the tile's in-image pixels packed into groups of 64): wave 0 walks
-// the list once per pixel (the same decisions, in the same order, as
-// k_blend), the weights of up to SGF_BUF entries collect in LDS, and the
-// eight waves then form out = W^T V on the FP32 matrix cores, each for its
-// share of the columns.  A walk longer than the buffer flushes it and the
-// next products add to the stored spectrum (only this workgroup writes
-// these pixels).
-// ---------------------------------------------------------------------------
-constexpr int SGF_WAVES = 8;
-constexpr int SGF_PIX = 64;
-constexpr int SGF_BATCH = 64;   // entries staged per walk step
-constexpr int SGF_BUF = 128;    // entries whose weights the LDS holds
-
-template <int CS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_blend_sg(
-    const GRec* __restrict__ rec, const uint32_t* __restrict__ plist, const uint2* __restrict__ ranges,
-    const float* __restrict__ attr, int64_t a_stride, int S, int Fc, int H, int W, int tw, int th, int TX,
-    float amin, float amax, float tmin, float* __restrict__ out, float* __restrict__ T_final,
-    uint32_t* __restrict__ n_last, uint32_t* __restrict__ n_contrib, int min_walk)
-{
-    const int tile = blockIdx.x, pg = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j4 = lane >> 4, l16 = lane & 15;
-    const int txi = tile % TX, tyi = tile / TX;
-    const int vw = min(tw, W - txi * tw), vh = min(th, H - tyi * th);
-    if (pg * SGF_PIX >= vw * vh) return;
-    if (min_walk > 0) {
-        // only groups whose walk (the stop positions a live pass recorded)
-        // is longer than min_walk entries
-        const int k = pg * SGF_PIX + lane;
-        const uint32_t st = k < vw * vh ? n_last[(tyi * th + k / vw) * W + txi * tw + k % vw] : 0u;
-        uint32_t mx = st;
-        for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 64));
-        if (mx <= (uint32_t)min_walk) return;
-    }
-    const uint2 rg = ranges[tile];
-    const size_t HW = (size_t)H * W;
-    const int F = Fc >> CS;
-    const int ncb = S * Fc / 16;  // 16-column blocks (Fc % 16 == 0)
-    const int cb_lo = wave * ncb / SGF_WAVES, cb_hi = (wave + 1) * ncb / SGF_WAVES;
-
-    __shared__ float s_w[SGF_BUF][SGF_PIX + 1];         // weights of the buffered entries
-    __shared__ uint32_t s_gb[SGF_BUF];                   // their Gaussians
-    __shared__ float s_t[SGF_WAVES][16][SGF_PIX + 1];   // per-wave output transpose
-    __shared__ double s_px[SGF_BATCH], s_py[SGF_BATCH], s_ca[SGF_BATCH], s_cb[SGF_BATCH], s_cc[SGF_BATCH];
-    __shared__ float s_sig[SGF_BATCH], s_att[SGF_BATCH];
-    __shared__ uint32_t s_g[SGF_BATCH];
-    __shared__ int s_pix[SGF_PIX];
-    __shared__ int s_walked, s_alldone;
-
-    if (threadIdx.x < SGF_PIX) {
-        const int k = pg * SGF_PIX + threadIdx.x;
-        s_pix[threadIdx.x] = k < vw * vh ? (tyi * th + k / vw) * W + txi * tw + k % vw : -1;
-    }
-    __syncthreads();
-    // the walking wave's pixel and state
-    const int wpix = s_pix[lane];
-    const double pcx = (wpix >= 0 ? wpix % W : 0) + 0.5, pcy = (wpix >= 0 ? wpix / W : 0) + 0.5;
-    const double halfW = 0.5 * W, Wd = (double)W;
-    float T = 1.0f;
-    uint32_t last = 0, cnt = 0;
-    bool done = wpix < 0;
-
-    // out = W^T V over the nbuf buffered entries for this wave's columns;
-    // add: add to what an earlier flush stored
-    auto contract = [&](int nbuf, bool add) {
-        const int nks = (nbuf + 3) >> 2;  // K-steps of 4 entries (rows past nbuf hold zero weights)
-        for (int cb = cb_lo; cb < cb_hi; ++cb) {
-            const int s = cb * 16 / Fc;
-            const int c0 = cb * 16 - s * Fc;
-            const CFloat* vb = (const CFloat*)(attr + s * a_stride + c0 + l16);
-            // the B operands of every K-step first (independent loads)
-            float bq[SGF_BUF / 4];
-#pragma unroll
-            for (int ks = 0; ks < SGF_BUF / 4; ++ks)
-                if (ks < nks) bq[ks] = vb[(size_t)s_gb[4 * ks + j4] * Fc];
-            f32x4 acc[4];
-#pragma unroll
-            for (int pb = 0; pb < 4; ++pb) acc[pb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int ks = 0; ks < SGF_BUF / 4; ++ks) {
-                if (ks < nks) {
-#pragma unroll
-                    for (int pb = 0; pb < 4; ++pb)
-                        acc[pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(s_w[4 * ks + j4][16 * pb + l16], bq[ks],
-                                                                       acc[pb], 0, 0, 0);
-                }
-            }
-            // lane holds out[pixel 16 pb + 4 j4 + r][column c0 + l16]: through
-            // LDS so that each lane stores its own pixel
-#pragma unroll
-            for (int pb = 0; pb < 4; ++pb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) s_t[wave][l16][16 * pb + 4 * j4 + r] = acc[pb][r];
-            wave_sync_lds();
-            const int px = s_pix[lane];
-            if (px >= 0) {
-                float* ob = out + ((size_t)s * F * HW << CS);
-                if constexpr (CS == 1) {
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        float2* o2 = (float2*)(ob + (((size_t)((c0 >> 1) + q) * HW + px) << 1));
-                        float2 v = float2{s_t[wave][2 * q][lane], s_t[wave][2 * q + 1][lane]};
-                        if (add) {
-                            const float2 o = *o2;
-                            v.x += o.x;
-                            v.y += o.y;
-                        }
-                        *o2 = v;
-                    }
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        float* o1 = ob + (size_t)(c0 + q) * HW + px;
-                        const float v = s_t[wave][q][lane];
-                        *o1 = add ? *o1 + v : v;
-                    }
-                }
-            }
-            wave_sync_lds();
-        }
-    };
-
-    int nbuf = 0;
-    bool stored = false, alldone = false;
-    for (uint32_t b0 = rg.x; b0 < rg.y && !alldone; b0 += SGF_BATCH) {
-        const int m = (int)min((uint32_t)SGF_BATCH, rg.y - b0);
-        if ((int)threadIdx.x < m) {
-            const uint32_t g = plist[b0 + threadIdx.x];
-            const GRec r = rec[g];
-            s_px[threadIdx.x] = r.px;
-            s_py[threadIdx.x] = r.py;
-            s_ca[threadIdx.x] = r.ca;
-            s_cb[threadIdx.x] = r.cb;
-            s_cc[threadIdx.x] = r.cc;
-            s_sig[threadIdx.x] = r.sigma;
-            s_att[threadIdx.x] = r.att;
-            s_g[threadIdx.x] = g;
-        }
-        __syncthreads();
-        if (wave == 0) {
-            // the walk, as in k_blend: stop before an entry that would take
-            // T below T_min; entries past the group's last live pixel are
-            // not buffered
-            int j = 0;
-            for (; j < m; ++j) {
-                if (__ballot(!done) == 0ull) break;
-                float wgt = 0.0f;
-                if (!done) {
-                    double dx = pcx - s_px[j];
-                    dx += dx >= halfW ? -Wd : (dx < -halfW ? Wd : 0.0);
-                    const double dy = pcy - s_py[j];
-                    const double qv = s_ca[j] * dx * dx + 2.0 * s_cb[j] * dx * dy + s_cc[j] * dy * dy;
-                    const float G = __builtin_amdgcn_exp2f((float)(-0.5 * LOG2E * qv));
-                    const float alpha = fminf(amax, s_sig[j] * G);
-                    const float Tn = T * (1.0f - alpha);
-                    const bool stop = alpha >= amin && Tn < tmin;
-                    const bool take = alpha >= amin && !stop;
-                    done = stop;
-                    wgt = take ? T * alpha * s_att[j] : 0.0f;
-                    T = take ? Tn : T;
-                    last = take ? b0 + j + 1 - rg.x : last;
-                    cnt += take ? 1u : 0u;
-                }
-                s_w[nbuf + j][lane] = wgt;
-                if (lane == 0) s_gb[nbuf + j] = s_g[j];
-            }
-            // zero weight rows up to the next multiple of 4 (valid Gaussians)
-            for (int k = j; k < ((j + 3) & ~3); ++k) {
-                s_w[nbuf + k][lane] = 0.0f;
-                if (lane == 0) s_gb[nbuf + k] = s_g[0];
-            }
-            const bool ad = __ballot(!done) == 0ull;
-            if (lane == 0) {
-                s_walked = j;
-                s_alldone = ad ? 1 : 0;
-            }
-        }
-        __syncthreads();
-        nbuf += s_walked;
-        alldone = s_alldone != 0;
-        const bool last_batch = alldone || b0 + SGF_BATCH >= rg.y;
-        if (last_batch || nbuf + SGF_BATCH > SGF_BUF) {
-            if (nbuf > 0) {
-                contract(nbuf, stored);
-                stored = true;
-            }
-            nbuf = 0;
-        }
-        __syncthreads();
-    }
-    if (!stored) {
-        // no entry reached the group: its spectrum is zero
-        const int px = s_pix[lane];
-        if (px >= 0) {
-            for (int cb = cb_lo; cb < cb_hi; ++cb) {
-                const int s = cb * 16 / Fc;
-                const int c0 = cb * 16 - s * Fc;
-                float* ob = out + ((size_t)s * F * HW << CS);
-                for (int q = 0; q < 16; ++q) ob[((size_t)((c0 + q) >> CS) * HW + px) * (1 << CS) + ((c0 + q) & CS)] = 0.0f;
-            }
-        }
-    }
-    if (wave == 0 && wpix >= 0) {
-        T_final[wpix] = T;
-        n_last[wpix] = last;
-        n_contrib[wpix] = cnt;
-    }
-}
-
 // Channel floats per workgroup: the largest power of two that divides F*c,
 // at most 64, or the caller's choice (a power of two up to 64 dividing F*c).
 // (The backward and the persistent batch kernel cap it at 32.)
@@ -784,69 +964,128 @@ int choose_chan_group(int Fc, int requested)
     return cg;
 }
 
+// Channel floats per workgroup of the compositing kernels: the caller's
+// choice where it is valid; else up to 8 channel floats go to k_blend in one
+// group (the smallest power of two that holds them), more to the matrix-core
+// kernel in blocks of 16, all columns of a set after one walk.  The walk over
+// the list is repeated for every group, so one partly empty group costs less
+// than several full ones: 10 channel
+// floats at 61,803 Gaussians, three receivers: 159 us in five groups of two,
+// 62 in one block of 16.
+int choose_blend_group(int Fc, int requested)
+{
+    if (requested > 0 && requested <= 64 && (requested & (requested - 1)) == 0 && Fc % requested == 0) return requested;
+    if (Fc > BLEND_ROW_CG) return (Fc + 15) / 16 * 16;
+    int cg = 1;
+    while (cg < Fc) cg *= 2;
+    return cg;
+}
+
+// Column ranges of the matrix-core kernel over `nb` column blocks: enough
+// waves to fill the chip several times over (12 are resident per CU), at
+// least MX_MIN_BLOCKS 16-column blocks after each walk, and a multiple of the
+// 8 XCDs where there are that many.
+constexpr int MX_WAVES = 16384, MX_MIN_BLOCKS = 4;
+static int mx_split(int64_t groups, int nb, int nv)
+{
+    int64_t r = std::min<int64_t>((MX_WAVES + groups - 1) / groups, (int64_t)nb * nv / MX_MIN_BLOCKS);
+    if (r >= 8) r = r / 8 * 8;
+    return (int)std::max<int64_t>(std::min<int64_t>(r, nb), 1);
+}
+
+// The addressing of the matrix-core form: 32-bit byte offsets where a set's
+// attributes and spectrum (n Gaussians) allow it and pairs are aligned, else
+// 64-bit; and MX_WIDE columns a lane where a set's complex columns divide and
+// are aligned for it.
+void blend_mx_form(BlendJob* J, int64_t n)
+{
+    const int64_t bytes = (std::max<int64_t>(n, (int64_t)J->H * J->W) + 1) * ((J->Fc + 31) / 16 * 16) * 4;
+    J->big = bytes >= 0x7FFFFFFFll || ((uintptr_t)J->out & 7) != 0;
+    J->nv = !J->big && J->C == 2 && J->Fc % (16 * MX_WIDE) == 0 && ((uintptr_t)J->attr & (4 * MX_WIDE - 1)) == 0 &&
+                    J->a_stride % MX_WIDE == 0
+                ? MX_WIDE
+                : 1;
+}
+
+static gs_status launch_mx(BlendJob J, const Layout& L, hipStream_t s, int min_walk)
+{
+    blend_mx_form(&J, L.n);
+    const int nb = (J.Fc + 16 * J.nv - 1) / (16 * J.nv) * (J.across ? J.nsets : 1), z = J.across ? 1 : J.nsets;
+    const int gpt = (L.tw * L.th) >> 6;
+    if (J.ncg == 0) J.ncg = mx_split((int64_t)L.T * gpt * z, nb, J.nv);
+    J.ncg = std::min(J.ncg, nb);
+    if ((int64_t)L.T * J.ncg > 0x7FFFFFFF) return GS_ERR_CAPACITY;
+    auto kern = J.big ? k_blend_mx<1, true> : (J.nv > 1 ? k_blend_mx<MX_WIDE, false> : k_blend_mx<1, false>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(L.T * J.ncg), 1, z), dim3(64 * gpt), 0, s, J, J.rec, J.plist, J.ranges,
+                       J.attr, J.out, J.T_final, J.n_last, J.n_contrib, min_walk);
+    return GS_OK;
+}
+
 gs_status launch_blend(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out,
                        hipStream_t s, const float* tgt, float* dpart, float* lpart, float lscale)
 {
     const int C = a.is_complex ? 2 : 1;
     const int Fc = a.n_chan * C;
-    if (!tgt && L.nq == 1 && Fc % 16 == 0 && !(p.options & GS_OPT_BLEND_PER_GROUP)) {
-        // every set over the one prepared geometry: the walk once per pixel
+    int cg = choose_blend_group(Fc, p.chan_group);
+    BlendJob J = make_blend_job(a, p, L, n_sets, ws, out);
+    const bool per_set = (p.options & GS_OPT_BLEND_PER_GROUP) != 0;
+    if (!tgt && (cg > BLEND_ROW_CG || (L.nq == 1 && Fc % 16 == 0 && !per_set))) {
+        // every column after a pixel's walk; over the one prepared geometry
+        // the columns of all sets
+        J.across = L.nq == 1 && !per_set;
+        J.ncg = !J.across && p.chan_group == cg ? Fc / cg : 0;
         void* tok;
         timing_begin(TK_BLEND, s, &tok);
-        auto kern = C == 2 ? k_blend_sg<1> : k_blend_sg<0>;
-        hipLaunchKernelGGL(kern, dim3(L.T, (L.tw * L.th) / SGF_PIX), dim3(64 * SGF_WAVES), 0, s,
-                           (const GRec*)(ws + L.rec), (const uint32_t*)(ws + L.plist), (const uint2*)(ws + L.ranges),
-                           a.data, a.query_stride, n_sets, Fc, L.H, L.W, L.tw, L.th, L.TX, p.alpha_min, p.alpha_max,
-                           p.T_min, out, (float*)(ws + L.T_final), (uint32_t*)(ws + L.n_last),
-                           (uint32_t*)(ws + L.n_contrib), 0);
+        const gs_status st = launch_mx(J, L, s, 0);
         timing_end(tok, s);
-        return GS_OK;
+        return st;
     }
-    int cg = choose_chan_group(Fc, p.chan_group);
-    if (tgt && cg > 32) cg = 32;  // the fused loss stage needs the registers of a 64-channel group
-    if (Fc / cg > 65535) return GS_ERR_CAPACITY;
-    BlendJob J = make_blend_job(a, p, L, n_sets, ws, out);
+    // (the fused loss stage runs in k_blend, whose groups end at 32)
+    if (tgt && cg > 32) cg = 32;
+    if (tgt && (cg & (cg - 1))) cg = cg > 16 ? 32 : 16;
+    const int ncg = (Fc + cg - 1) / cg;
+    if (ncg > 65535) return GS_ERR_CAPACITY;
     J.cg = cg;
-    J.ncg = Fc / cg;
+    J.ncg = ncg;
     J.tgt = tgt;
     J.dpart = dpart;
     J.lpart = lpart;
     J.lnp = L.T * ((L.tw * L.th) >> 6);
     J.lscale = lscale;
-    dim3 grid(L.T, Fc / cg, n_sets), block(L.tw * L.th);
+    dim3 grid(L.T, ncg, n_sets), block(L.tw * L.th);
 #define ARGS J.rec, J.plist, J.ranges, J.attr, J.out, J.T_final, J.n_last, J.n_contrib
     void* tok;
     timing_begin(TK_BLEND, s, &tok);
-    auto go = [&](auto fz) {
-        constexpr bool FZ = decltype(fz)::value;
+    if (tgt) {
         switch (cg) {
-            case 1: hipLaunchKernelGGL((k_blend<1, FZ>), grid, block, 0, s, J, ARGS); break;
-            case 2: hipLaunchKernelGGL((k_blend<2, FZ>), grid, block, 0, s, J, ARGS); break;
-            case 4: hipLaunchKernelGGL((k_blend<4, FZ>), grid, block, 0, s, J, ARGS); break;
-            case 8: hipLaunchKernelGGL((k_blend<8, FZ>), grid, block, 0, s, J, ARGS); break;
-            case 16: hipLaunchKernelGGL((k_blend<16, FZ>), grid, block, 0, s, J, ARGS); break;
-            case 32: hipLaunchKernelGGL((k_blend<32, FZ>), grid, block, 0, s, J, ARGS); break;
-            default: hipLaunchKernelGGL((k_blend<64, FZ>), grid, block, 0, s, J, ARGS); break;
+            case 1: hipLaunchKernelGGL((k_blend<1, true>), grid, block, 0, s, J, ARGS); break;
+            case 2: hipLaunchKernelGGL((k_blend<2, true>), grid, block, 0, s, J, ARGS); break;
+            case 4: hipLaunchKernelGGL((k_blend<4, true>), grid, block, 0, s, J, ARGS); break;
+            case 8: hipLaunchKernelGGL((k_blend<8, true>), grid, block, 0, s, J, ARGS); break;
+            case 16: hipLaunchKernelGGL((k_blend<16, true>), grid, block, 0, s, J, ARGS); break;
+            default: hipLaunchKernelGGL((k_blend<32, true>), grid, block, 0, s, J, ARGS); break;
         }
-    };
-    if (tgt) go(std::true_type{});
-    else go(std::false_type{});
+    } else {
+        switch (cg) {
+            case 1: hipLaunchKernelGGL((k_blend<1, false>), grid, block, 0, s, J, ARGS); break;
+            case 2: hipLaunchKernelGGL((k_blend<2, false>), grid, block, 0, s, J, ARGS); break;
+            case 4: hipLaunchKernelGGL((k_blend<4, false>), grid, block, 0, s, J, ARGS); break;
+            default: hipLaunchKernelGGL((k_blend<8, false>), grid, block, 0, s, J, ARGS); break;
+        }
+    }
     timing_end(tok, s);
 #undef ARGS
     return GS_OK;
 }
 
-// k_blend_sg over the groups whose walk (live-pass stop positions) is longer
-// than min_walk entries only
+// the shared-geometry compositing over the groups whose walk (live-pass stop
+// positions) is longer than min_walk entries only
 void launch_blend_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out,
                           int min_walk, hipStream_t s)
 {
-    auto kern = a.is_complex ? k_blend_sg<1> : k_blend_sg<0>;
-    hipLaunchKernelGGL(kern, dim3(L.T, (L.tw * L.th) / SGF_PIX), dim3(64 * SGF_WAVES), 0, s,
-                       (const GRec*)(ws + L.rec), (const uint32_t*)(ws + L.plist), (const uint2*)(ws + L.ranges),
-                       a.data, a.query_stride, n_sets, a.n_chan * (a.is_complex ? 2 : 1), L.H, L.W, L.tw, L.th, L.TX,
-                       p.alpha_min, p.alpha_max, p.T_min, out, (float*)(ws + L.T_final), (uint32_t*)(ws + L.n_last),
-                       (uint32_t*)(ws + L.n_contrib), min_walk);
+    BlendJob J = make_blend_job(a, p, L, n_sets, ws, out);
+    J.across = 1;
+    launch_mx(J, L, s, min_walk);
 }
 
 void launch_blend_persist(const BlendJob* jobs, int njobs, uint32_t total, uint32_t* counter,

@@ -41,6 +41,8 @@ struct BlendJob {
     const float* attr;
     int64_t a_stride;
     int Fc, C, H, W, tw, th, TX, T, cg, ncg, nsets, shared_geo;
+    int nv, big;  // matrix-core form: columns a lane loads at once; 64-bit addressing
+    int across;  // a column range runs over the columns of every set (one shared geometry)
     float amin, amax, tmin;
     float* out;
     float* T_final;
@@ -195,6 +197,10 @@ gs_status check_forward(const gs_scene* sc, const gs_attrs* a, const gs_queries*
 void enqueue_prepare(const gs_scene* scene, const gs_queries* queries, const gs_grid* grid, const gs_params* prm,
                      const Layout& L, char* ws, hipStream_t s);
 int choose_chan_group(int Fc, int requested);
+int choose_blend_group(int Fc, int requested);
+struct BlendJob;
+void blend_mx_form(BlendJob* J, int64_t n);
+constexpr int BLEND_ROW_CG = 8;  // channel floats up to which k_blend composites; the matrix-core form beyond
 BlendJob make_blend_job(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out);
 void launch_blend_persist(const BlendJob* jobs, int njobs, uint32_t total, uint32_t* counter,
                           unsigned long long* done_ts, int workgroups, int block, hipStream_t s);

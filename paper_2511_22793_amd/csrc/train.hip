@@ -21,9 +21,9 @@
 // alpha for every (entry, pixel) of the group's walk (all four waves), forms
 // the prefix transmittance and the weights (one wave), then walks its column
 // range in rounds of four 16-column blocks, one per wave:
-//   (F) zhat on the FP32 matrix cores (the product of k_blend_sg, same
-//       operands and K order, so an optional spectrum store is bit-identical
-//       to the compositing kernel's), the target read, g, the loss partial;
+//   (F) zhat on the FP32 matrix cores (the product of k_blend_mx, same
+//       order, so an optional spectrum store is bit-identical to the
+//       compositing kernel's), the target read, g, the loss partial;
 //   (D) dL/dv over the group's 64 pixels from g in registers, one atomic per
 //       (entry, column) of the unit;
 //   (G) g of all four blocks goes through LDS so that each wave adds GV for
@@ -349,10 +349,10 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb) z[pb] = f32x4t{0.0f, 0.0f, 0.0f, 0.0f};
         if (own) {
-            // (F) zhat = W^T V, in chains of 128 entries added in list order
-            // (the compositing kernel's buffer flushes, so that the stored
-            // spectrum is bit-identical to it); the first chain's V words
-            // were loaded with the previous round
+            // (F) zhat = W^T V, one chain of fused multiply-adds in list order
+            // (as in the compositing kernel, so that the stored spectrum is
+            // bit-identical to it); the V words of its first KCH steps were
+            // loaded with the previous round
             const __amdgpu_buffer_rsrc_t rv = tr_rsrc(A.attr + s * A.a_stride);
             for (int kc = 0; kc < nks; kc += KCH) {
                 if (kc > 0) {
@@ -360,22 +360,17 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
                     for (int q = 0; q < KCH; ++q)
                         if (kc + q < nks) bq[q] = tr_ld(rv, (L.voff[4 * (kc + q) + j4] + (uint32_t)(c0 + l16)) * 4u);
                 }
-                f32x4t zc[4];
-#pragma unroll
-                for (int pb = 0; pb < 4; ++pb) zc[pb] = f32x4t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int q = 0; q < KCH; ++q) {
                     if (kc + q < nks) {
                         const int ks = kc + q;
                         const float4 wa = *(const float4*)&s_w[4 * ks + j4][4 * l16];
-                        zc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.x, bq[q], zc[0], 0, 0, 0);
-                        zc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.y, bq[q], zc[1], 0, 0, 0);
-                        zc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.z, bq[q], zc[2], 0, 0, 0);
-                        zc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.w, bq[q], zc[3], 0, 0, 0);
+                        z[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.x, bq[q], z[0], 0, 0, 0);
+                        z[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.y, bq[q], z[1], 0, 0, 0);
+                        z[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.z, bq[q], z[2], 0, 0, 0);
+                        z[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.w, bq[q], z[3], 0, 0, 0);
                     }
                 }
-#pragma unroll
-                for (int pb = 0; pb < 4; ++pb) z[pb] = kc == 0 ? zc[pb] : zc[pb] + z[pb];
             }
             // target, g, loss partial (column c0 + l16 = channel f, re/im)
             const int c = c0 + l16;
