@@ -45,8 +45,11 @@ __device__ __forceinline__ float adam_one(float p, float g, float& m, float& v, 
     m = (float)md;
     v = (float)vd;
     // square root and reciprocal from the hardware estimates (about 24 bits)
-    // and one Newton step each: 48 bits, and no scaling sequences
-    const double x = vd * K.ic2;
+    // and one Newton step each: 48 bits, and no scaling sequences.  A
+    // second moment that overflowed to infinity makes no update, as a finite
+    // bound that the Newton steps can take
+    double x = vd * K.ic2;
+    x = x > 1e300 ? 1e300 : x;
     double y = __builtin_amdgcn_rsq(x);
     y = y * fma(-0.5 * x * y, y, 1.5);
     const double den = (x > 0.0 ? x * y : x) + K.eps;

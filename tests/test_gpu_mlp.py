@@ -240,3 +240,29 @@ def test_adam_matches_oracle_and_refreshes_bf16():
     for k in range(3):
         assert np.allclose(tp[k].cpu().numpy(), ref[k], rtol=1e-5, atol=1e-6)
     assert np.array_equal(sh.cpu().numpy().view(np.uint16), gm.bf16_bits(tp[1].cpu().numpy()))
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 259])
+def test_adam_extreme_gradients(n):
+    """A zero, a tiny, an ordinary and a huge gradient, the last with a second
+    moment that overflows FP32: later updates of that element are 0 while its
+    moment stays infinite, the rest follow the oracle.  Bound: half a unit in
+    the last place of p per step (p is rounded once), 2^-24 |p|, and 2e-6 of
+    the rate for the FP32 moments (a few roundings) and the FP32 betas."""
+    lr = 1e-3
+    g = np.resize(np.array([0.0, 1e-18, 0.3, 1e25], np.float32), n)
+    p0 = np.linspace(-1.0, 1.0, n).astype(np.float32)
+    p, m, v = torch.from_numpy(p0.copy()).cuda(), torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    ref, rm, rv = p0.astype(np.float64), np.zeros(n), np.zeros(n)
+    huge = g > 1e20
+    for t in range(1, 4):
+        before = p.cpu().numpy()
+        gm.adam_step([(p, torch.from_numpy(g).cuda(), m, v, None, lr)], t)
+        new, rm, rv = mlp_ref.adam(ref, g.astype(np.float64), rm, rv, t, lr)
+        got = p.cpu().numpy()
+        assert np.isfinite(got).all()
+        if t > 1:
+            assert np.isinf(v.cpu().numpy()[huge]).all() and np.array_equal(got[huge], before[huge])
+        ref = new
+        tol = t * (2.0 ** -24 * np.maximum(np.abs(ref), np.abs(got)) + 2e-6 * lr)
+        assert (np.abs(got - ref) <= tol)[~huge].all()
