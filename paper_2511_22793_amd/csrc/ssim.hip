@@ -15,10 +15,18 @@
 // each map zero outside the image, divided by the pixel count.
 //
 // One workgroup per (32 x 16 tile, channel, set), everything in LDS: the
-// inputs with a 10-pixel halo, the five filtered maps on the tile with a
-// 5-pixel halo (rows, then columns), the three derivative maps there, and
-// their filtered values on the tile.  Per-workgroup sums of |x - y| and of s
-// go to a partial buffer summed in a fixed order by a second kernel.
+// inputs with a 10-pixel halo, the four row-filtered maps on the tile with a
+// 5-pixel halo in columns, the three derivative maps on the tile with a
+// 5-pixel halo, and their filtered values on the tile.  Every thread filters
+// a run of neighbouring outputs along the filter's direction, so a value
+// leaves LDS about 3 times instead of once per tap, and the column filter
+// goes on to the derivative maps in registers.  The
+// inputs, the row maps and the derivative maps take each other's place (24 KB
+// of LDS, five workgroups per CU).  x^2 and y^2 are only needed summed.
+// Bound: FP32 multiply-adds at one per lane and issue (about 310 per pixel
+// with the halos).  32 spectra of 90 x 360: 76 us with one LDS read per tap,
+// 29 us so.  Per-workgroup sums of |x - y| and of s go to a
+// partial buffer summed in a fixed order by a second kernel.
 #include "common.h"
 
 namespace gs {
@@ -29,10 +37,30 @@ constexpr int SS_IW = SS_TW + 4 * SS_R;          // input columns (52)
 constexpr int SS_IH = SS_TH + 4 * SS_R;          // input rows (36)
 constexpr int SS_MW = SS_TW + 2 * SS_R;          // map columns (42)
 constexpr int SS_MH = SS_TH + 2 * SS_R;          // map rows (26)
+// outputs per thread of the four filter passes, and the threads they take
+constexpr int SS_P1 = 7, SS_S1 = SS_MW / SS_P1;                  // rows of inputs: 6 runs x 36 rows
+constexpr int SS_P2 = 5, SS_S2 = (SS_MH + SS_P2 - 1) / SS_P2;    // columns of maps: 6 runs x 42 columns
+constexpr int SS_P3 = 4, SS_S3 = SS_TW / SS_P3;                  // rows of derivatives: 8 runs x 26 rows
+constexpr int SS_P4 = 2, SS_S4 = SS_TH / SS_P4;                  // columns of derivatives: 8 runs x 32 columns
+static_assert(SS_MW % SS_P1 == 0 && SS_S1 * SS_IH <= 256 && SS_S2 * SS_MW <= 256 && SS_S3 * SS_MH <= 256 &&
+                  SS_S4 * SS_TW == 256,
+              "ssim thread layout");
 
 struct SsimWin {
     float w[SS_K];
 };
+
+// o[i] = sum_k w[k] v[i + k], the taps in order
+template <int N>
+__device__ __forceinline__ void ss_filter(const float* v, const SsimWin& win, float* o)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < SS_K; ++k)
+#pragma unroll
+        for (int i = 0; i < N; ++i) o[i] = fmaf(win.w[k], v[i + k], o[i]);
+}
 
 __global__ __launch_bounds__(256) void k_l1_ssim(const float* __restrict__ x, const float* __restrict__ y, int H,
                                                  int W, int tiles_x, int ntiles, SsimWin win, float C1, float C2,
@@ -44,100 +72,148 @@ __global__ __launch_bounds__(256) void k_l1_ssim(const float* __restrict__ x, co
     const size_t HW = (size_t)H * W;
     x += img * HW;
     y += img * HW;
-    __shared__ float s_x[SS_IH][SS_IW], s_y[SS_IH][SS_IW];
-    __shared__ float s_h[5][SS_IH][SS_MW];   // row-filtered maps; later the derivative maps
-    __shared__ float s_m[5][SS_MH][SS_MW];   // filtered maps; later the row-filtered derivative maps
+    // in turn: the inputs; the row-filtered maps; the derivative maps and,
+    // behind them, their row-filtered form
+    __shared__ float s_h[4 * SS_IH * SS_MW];
+    float (*s_x)[SS_IW] = (float (*)[SS_IW])s_h, (*s_y)[SS_IW] = s_x + SS_IH;
+    float (*s_r)[SS_IH][SS_MW] = (float (*)[SS_IH][SS_MW])s_h;
+    float (*s_d)[SS_MH][SS_MW] = (float (*)[SS_MH][SS_MW])s_h;
+    float (*s_f)[SS_MH][SS_TW] = (float (*)[SS_MH][SS_TW])(s_h + 3 * SS_MH * SS_MW);
+    static_assert(3 * SS_MH * (SS_MW + SS_TW) <= 4 * SS_IH * SS_MW && 2 * SS_IH * SS_IW <= 4 * SS_IH * SS_MW,
+                  "ssim LDS");
     __shared__ float s_red[2][4];
     const int t = threadIdx.x;
 
-    for (int i = t; i < SS_IH * SS_IW; i += 256) {
-        const int r = i / SS_IW, c = i % SS_IW;
+    constexpr int NL = (SS_IH * SS_IW + 255) / 256;
+    float lx[NL], ly[NL];
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+        const int i = u * 256 + t, r = i / SS_IW, c = i % SS_IW;
         const int gr = ty0 - 2 * SS_R + r, gc = tx0 - 2 * SS_R + c;
-        const bool in = gr >= 0 && gr < H && gc >= 0 && gc < W;
-        s_x[r][c] = in ? x[(size_t)gr * W + gc] : 0.0f;
-        s_y[r][c] = in ? y[(size_t)gr * W + gc] : 0.0f;
+        const bool in = i < SS_IH * SS_IW && gr >= 0 && gr < H && gc >= 0 && gc < W;
+        lx[u] = in ? x[(size_t)gr * W + gc] : 0.0f;
+        ly[u] = in ? y[(size_t)gr * W + gc] : 0.0f;
     }
-    __syncthreads();
-    // rows: x, y, x^2, y^2, x y filtered along the columns
-    for (int i = t; i < SS_IH * SS_MW; i += 256) {
-        const int r = i / SS_MW, c = i % SS_MW;
-        float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f, a4 = 0.0f;
 #pragma unroll
-        for (int k = 0; k < SS_K; ++k) {
-            const float xv = s_x[r][c + k], yv = s_y[r][c + k], w = win.w[k];
-            a0 = fmaf(w, xv, a0);
-            a1 = fmaf(w, yv, a1);
-            a2 = fmaf(w, xv * xv, a2);
-            a3 = fmaf(w, yv * yv, a3);
-            a4 = fmaf(w, xv * yv, a4);
+    for (int u = 0; u < NL; ++u) {
+        const int i = u * 256 + t;
+        if (i < SS_IH * SS_IW) {
+            (&s_x[0][0])[i] = lx[u];
+            (&s_y[0][0])[i] = ly[u];
         }
-        s_h[0][r][c] = a0;
-        s_h[1][r][c] = a1;
-        s_h[2][r][c] = a2;
-        s_h[3][r][c] = a3;
-        s_h[4][r][c] = a4;
     }
     __syncthreads();
-    for (int i = t; i < 5 * SS_MH * SS_MW; i += 256) {
-        const int q = i / (SS_MH * SS_MW), rc = i % (SS_MH * SS_MW);
-        const int r = rc / SS_MW, c = rc % SS_MW;
-        float a = 0.0f;
+    // rows: x, y, x^2 + y^2, x y filtered along the columns; the thread's own
+    // two pixels stay in registers for the end
+    const int r4 = t / SS_TW * SS_P4, c4 = t % SS_TW;
+    float px[SS_P4], py[SS_P4];
 #pragma unroll
-        for (int k = 0; k < SS_K; ++k) a = fmaf(win.w[k], s_h[q][r + k][c], a);
-        s_m[q][r][c] = a;
+    for (int i = 0; i < SS_P4; ++i) {
+        px[i] = s_x[r4 + i + 2 * SS_R][c4 + 2 * SS_R];
+        py[i] = s_y[r4 + i + 2 * SS_R][c4 + 2 * SS_R];
+    }
+    const bool act1 = t < SS_S1 * SS_IH;
+    const int r1 = act1 ? t / SS_S1 : 0, c1 = t % SS_S1 * SS_P1;
+    float xv[SS_P1 + SS_K - 1], yv[SS_P1 + SS_K - 1];
+#pragma unroll
+    for (int k = 0; k < SS_P1 + SS_K - 1; ++k) {
+        xv[k] = s_x[r1][c1 + k];
+        yv[k] = s_y[r1][c1 + k];
+    }
+    __syncthreads();  // the inputs are read
+    if (act1) {
+        float p[SS_P1 + SS_K - 1], o[SS_P1];
+        auto put = [&](int q, const float* v) {
+            ss_filter<SS_P1>(v, win, o);
+#pragma unroll
+            for (int i = 0; i < SS_P1; ++i) s_r[q][r1][c1 + i] = o[i];
+        };
+        put(0, xv);
+        put(1, yv);
+#pragma unroll
+        for (int k = 0; k < SS_P1 + SS_K - 1; ++k) p[k] = fmaf(xv[k], xv[k], yv[k] * yv[k]);
+        put(2, p);
+#pragma unroll
+        for (int k = 0; k < SS_P1 + SS_K - 1; ++k) p[k] = xv[k] * yv[k];
+        put(3, p);
     }
     __syncthreads();
-    // SSIM and its derivative maps on the tile plus the 5-pixel halo (zero
-    // outside the image); the SSIM sum over the tile's own pixels
+    // columns, then SSIM and its derivative maps on the tile plus the 5-pixel
+    // halo (zero outside the image); the SSIM sum over the tile's own pixels
     float ssum = 0.0f, l1sum = 0.0f;
-    for (int i = t; i < SS_MH * SS_MW; i += 256) {
-        const int r = i / SS_MW, c = i % SS_MW;
-        const int gr = ty0 - SS_R + r, gc = tx0 - SS_R + c;
-        float da = 0.0f, db = 0.0f, dc = 0.0f;
-        if (gr >= 0 && gr < H && gc >= 0 && gc < W) {
-            const float mx = s_m[0][r][c], my = s_m[1][r][c];
-            const float sxx = s_m[2][r][c] - mx * mx, syy = s_m[3][r][c] - my * my, sxy = s_m[4][r][c] - mx * my;
-            const float A1 = 2.0f * mx * my + C1, A2 = 2.0f * sxy + C2;
-            const float B1 = mx * mx + my * my + C1, B2 = sxx + syy + C2;
-            const float s = (A1 * A2) / (B1 * B2);
-            da = s * (2.0f * my / A1 - 2.0f * my / A2 - 2.0f * mx / B1 + 2.0f * mx / B2);
-            db = -s / B2;
-            dc = 2.0f * s / A2;
-            if (r >= SS_R && r < SS_R + SS_TH && c >= SS_R && c < SS_R + SS_TW) ssum += s;
+    const int r2 = t / SS_MW * SS_P2, c2 = t % SS_MW;
+    float d[3][SS_P2];
+    if (t < SS_S2 * SS_MW) {
+        float m[4][SS_P2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v[SS_P2 + SS_K - 1];
+#pragma unroll
+            for (int k = 0; k < SS_P2 + SS_K - 1; ++k) v[k] = r2 + k < SS_IH ? s_r[q][r2 + k][c2] : 0.0f;
+            ss_filter<SS_P2>(v, win, m[q]);
         }
-        s_h[0][r][c] = da;
-        s_h[1][r][c] = db;
-        s_h[2][r][c] = dc;
+#pragma unroll
+        for (int i = 0; i < SS_P2; ++i) {
+            const int r = r2 + i, gr = ty0 - SS_R + r, gc = tx0 - SS_R + c2;
+            d[0][i] = d[1][i] = d[2][i] = 0.0f;
+            if (r < SS_MH && gr >= 0 && gr < H && gc >= 0 && gc < W) {
+                const float mx = m[0][i], my = m[1][i];
+                const float m2 = mx * mx + my * my, sxy = m[3][i] - mx * my;
+                const float A1 = 2.0f * mx * my + C1, A2 = 2.0f * sxy + C2;
+                const float B1 = m2 + C1, B2 = m[2][i] - m2 + C2;
+                const float s = (A1 * A2) / (B1 * B2);
+                const float iA2 = 2.0f / A2, iB2 = 1.0f / B2;
+                d[0][i] = s * (my * (2.0f / A1 - iA2) - 2.0f * mx * (1.0f / B1 - iB2));
+                d[1][i] = -s * iB2;
+                d[2][i] = s * iA2;
+                if (r >= SS_R && r < SS_R + SS_TH && c2 >= SS_R && c2 < SS_R + SS_TW) ssum += s;
+            }
+        }
+    }
+    __syncthreads();  // the row maps are read
+    if (t < SS_S2 * SS_MW) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int i = 0; i < SS_P2; ++i)
+                if (r2 + i < SS_MH) s_d[q][r2 + i][c2] = d[q][i];
     }
     __syncthreads();
     // the derivative maps filtered along the columns (tile columns only)
-    for (int i = t; i < 3 * SS_MH * SS_TW; i += 256) {
-        const int q = i / (SS_MH * SS_TW), rc = i % (SS_MH * SS_TW);
-        const int r = rc / SS_TW, c = rc % SS_TW;
-        float a = 0.0f;
+    if (t < SS_S3 * SS_MH) {
+        const int r = t / SS_S3, c0 = t % SS_S3 * SS_P3;
 #pragma unroll
-        for (int k = 0; k < SS_K; ++k) a = fmaf(win.w[k], s_h[q][r][c + k], a);
-        s_m[q][r][c] = a;
+        for (int q = 0; q < 3; ++q) {
+            float v[SS_P3 + SS_K - 1], o[SS_P3];
+#pragma unroll
+            for (int k = 0; k < SS_P3 + SS_K - 1; ++k) v[k] = s_d[q][r][c0 + k];
+            ss_filter<SS_P3>(v, win, o);
+#pragma unroll
+            for (int i = 0; i < SS_P3; ++i) s_f[q][r][c0 + i] = o[i];
+        }
     }
     __syncthreads();
-    for (int i = t; i < SS_TH * SS_TW; i += 256) {
-        const int r = i / SS_TW, c = i % SS_TW;
-        const int gr = ty0 + r, gc = tx0 + c;
-        if (gr >= H || gc >= W) continue;
-        float ga = 0.0f, gb = 0.0f, gcc = 0.0f;
+    {
+        const int gc = tx0 + c4;
+        float g[3][SS_P4];
 #pragma unroll
-        for (int k = 0; k < SS_K; ++k) {
-            ga = fmaf(win.w[k], s_m[0][r + k][c], ga);
-            gb = fmaf(win.w[k], s_m[1][r + k][c], gb);
-            gcc = fmaf(win.w[k], s_m[2][r + k][c], gcc);
+        for (int q = 0; q < 3; ++q) {
+            float v[SS_P4 + SS_K - 1];
+#pragma unroll
+            for (int k = 0; k < SS_P4 + SS_K - 1; ++k) v[k] = s_f[q][r4 + k][c4];
+            ss_filter<SS_P4>(v, win, g[q]);
         }
-        const float xv = s_x[r + 2 * SS_R][c + 2 * SS_R], yv = s_y[r + 2 * SS_R][c + 2 * SS_R];
-        const float d = xv - yv;
-        l1sum += fabsf(d);
-        if (grad) {
-            const float sg = d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f);
-            const float dss = ga + 2.0f * xv * gb + yv * gcc;
-            grad[img * HW + (size_t)gr * W + gc] = gx_l1 * sg - gx_ssim * dss;
+#pragma unroll
+        for (int i = 0; i < SS_P4; ++i) {
+            const int gr = ty0 + r4 + i;
+            if (gr >= H || gc >= W) continue;
+            const float e = px[i] - py[i];
+            l1sum += fabsf(e);
+            if (grad) {
+                const float sg = e > 0.0f ? 1.0f : (e < 0.0f ? -1.0f : 0.0f);
+                const float dss = g[0][i] + 2.0f * px[i] * g[1][i] + py[i] * g[2][i];
+                grad[img * HW + (size_t)gr * W + gc] = gx_l1 * sg - gx_ssim * dss;
+            }
         }
     }
     // workgroup sums (fixed order)
