@@ -1,5 +1,5 @@
 // Backward of the front-to-back compositing (Eq. (3)), one workgroup per
-// (tile, channel group, attribute set), one thread per pixel.
+// (64 pixels of a tile, channel group, attribute set).
 //
 // With c_k = a_k sum_f g_f v_{k,f} (g = dL/dout of the pixel, summed over
 // the group's channels) and T_k the transmittance in front of entry k:
@@ -14,23 +14,20 @@
 // form q the gradient reaches the pixel-space centre and the conic.
 //
 // Per list entry the per-pixel terms are summed over the wave by a
-// butterfly reduce-scatter (every lane ends with one summed value), the
-// four waves are combined in LDS, and each batch of entries is flushed once
-// per workgroup: attribute gradients by atomics, geometric terms into a
-// per-pair accumulator (only the workgroups of one tile share an address)
-// that a second pass folds into the per-Gaussian sums.  The nearest
-// Gaussians cover every tile, so per-wave atomics would serialise on a few
-// addresses.
+// butterfly reduce-scatter (every lane ends with one summed value) and leave
+// by atomics: geometric terms into a per-pair accumulator (only the
+// workgroups of one tile share an address) that a second pass folds into the
+// per-Gaussian sums, attribute gradients into the Gaussian's row.  The
+// nearest Gaussians cover every tile, so per-Gaussian geometric atomics
+// would serialise on a few addresses.
 #include <type_traits>
 
 #include "common.h"
+#include "walk.h"
 
 namespace gs {
 
 constexpr double LOG2E_B = 1.4426950408889634;
-
-// read-only attribute rows through the scalar/constant path where uniform
-typedef __attribute__((address_space(4))) const float CFloatB;
 
 // The same reduce-scatter for 8 values without the LDS crossbar: lane
 // halves and quarter rows are exchanged with v_permlane32_swap /
@@ -75,14 +72,37 @@ __device__ __forceinline__ void wave_reduce_scatter8(float* x, int lane)
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Entries per matrix-core step of the attribute gradient (MFMA path), and
-// entries staged in LDS per batch (a small batch keeps the LDS footprint,
-// and so the occupancy, reasonable).
-constexpr int BWD_SUB = 16;
-constexpr int BWD_BATCH = 64;
+constexpr int BWD_WAVES = 4;                      // waves that share 64 pixels
+constexpr int BWD_SUB = WALK_BATCH / BWD_WAVES;   // entries of a batch per wave, at most
 
+// A queued entry: the walk's record and the FP32 conic for the gradient factors.
+struct alignas(16) BwdRec {
+    double px, py, ca, cb2, cc;
+    float sigma, att;
+    float caf, cbf, ccf;
+    uint32_t pos, g;  // place in the tile's list; Gaussian
+};
+
+// One workgroup per (64 pixels of a tile, channel group, set).  Walks are
+// short (40 - 70 entries where the opacity saturates) but a few are ten times
+// longer, and one wave spends ~900 cycles per entry on the gradient terms and
+// their sums over the wave, so a workgroup per tile with a wave per 64 pixels
+// lasted as long as its longest walk.  Here four waves share the pixels: per batch of 64
+// list entries each tests all against the pixels' box, takes a contiguous
+// quarter of those that reach it, forms the transmittance product and the
+// prefix sum P of its quarter, and after one exchange knows T and P in front
+// of it (P = P_0 + T_0 P_local).  The sums go to memory by atomics straight
+// from the wave: geometric terms into the pair's row (only the workgroups of
+// one tile share it), attribute gradients into the Gaussian's.
+// CG >= 16: gv = v . g per (entry, pixel) and the attribute gradient
+// dA[e][f] = sum_p w[p][e] g[p][f] are products on the FP32 matrix cores
+// (v_mfma_f32_16x16x4_f32), with g and w in LDS; smaller groups reduce over
+// the wave with the butterfly.
+// 16 receivers of 50,000 Gaussians at 90 x 360, one channel: 258 us with a
+// wave per 64 pixels and every entry of the tile walked, 163 us so; 4
+// receivers of 20,000, 32 channel floats: 557 us, 116 us so.
 template <int CG>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_blend_bwd(
+__global__ __launch_bounds__(64 * BWD_WAVES) __attribute__((amdgpu_waves_per_eu(CG == 64 ? 3 : 4))) void k_blend_bwd(
     const GRec* __restrict__ rec, size_t s_rec, const uint32_t* __restrict__ plist, size_t s_plist,
     const uint2* __restrict__ ranges, size_t s_ranges, const float* __restrict__ attr, int64_t a_stride,
     int Fc, int C, int H, int W, int tw, int th, int TX, float amin, float amax,
@@ -90,258 +110,275 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const float* __restrict__ mgrad, float gscale, const uint32_t* __restrict__ n_last, size_t s_pix,
     float* __restrict__ gacc, size_t s_gacc, float* __restrict__ d_attr, int64_t da_stride, int shared_geo)
 {
-    // dL/dout of the element at idx = the elementwise part (read, or formed
-    // from the output and the target) + the set's channel-mean term, which
-    // the callers load once per channel (mg)
-    auto upstream = [&](size_t idx) -> float { return tgt ? gscale * (out[idx] - tgt[idx]) : dout[idx]; };
-    // plus the channel-mean term m_f of the set (0 without mgrad).  It is
-    // not added to the per-pixel operands (that costs a quarter of the kernel
-    // time in register pressure) but folded in exactly by linearity:
-    //   D     += sum_f m_f out_f                    (per pixel, m uniform)
-    //   gv_e  += sum_f m_f v_{e,f}                  (per entry, at staging)
-    //   dL/dv_{e,f} += m_f sum_p w_{p,e}            (per entry, at the flush)
-    auto mean_term = [&](int ch) -> float { return mgrad ? mgrad[(size_t)blockIdx.z * Fc + ch] : 0.0f; };
-    // CG >= 16: the attribute gradient of a run of BWD_SUB entries,
-    // dA[e][f] = sum_p w[p][e] g[p][f], is a 16 x CG x 64 product per wave
-    // on the FP32 matrix cores (v_mfma_f32_16x16x4_f32); w goes through LDS.
-    // Smaller groups reduce over the wave with the butterfly.
     constexpr bool MFMA = CG >= 16;
     constexpr int NB = MFMA ? CG / 16 : 1;
-    const int tile = blockIdx.x, cg = blockIdx.y, set = blockIdx.z;
+    // entries evaluated together: 4 where the registers hold them
+    constexpr int BWD_STEP = CG == 1 ? 4 : 2;
+    const int npb = tw * th >> 6;  // 64-pixel boxes per tile
+    const int tile = blockIdx.x / npb, box_i = blockIdx.x % npb, cg = blockIdx.y, set = blockIdx.z;
     const int q = shared_geo ? 0 : set;
-    const int nthr = tw * th;
     const int txi = tile % TX, tyi = tile / TX;
-    const int lx = threadIdx.x % tw, ly = threadIdx.x / tw;
-    const int col = txi * tw + lx, row = tyi * th + ly;
+    WaveBox box;
+    if (!wave_box(box_i, txi, tyi, tw, th, H, W, box)) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = 64 * box_i + lane;
+    const int col = txi * tw + t % tw, row = tyi * th + t / tw;
     const bool inside = col < W && row < H;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint2 rg = ranges[q * s_ranges + tile];
     const double pcx = col + 0.5, pcy = row + 0.5, halfW = 0.5 * W;
     rec += q * s_rec;
-    plist += q * s_plist;
-    gacc += q * s_gacc;
-    const float* A = attr + set * a_stride + cg * CG;
-    float* dA = d_attr + set * da_stride + cg * CG;
+    plist += q * s_plist + rg.x;
+    gacc += q * s_gacc + (size_t)rg.x * 8;
+    const int ch0 = cg * CG, nch = min(CG, Fc - ch0);  // the last group may be partly filled
+    const float* A = attr + set * a_stride + ch0;
+    float* dA = d_attr + set * da_stride + ch0;
     const size_t HW = (size_t)H * W, pix = inside ? (size_t)row * W + col : 0;
-    // (the channel split below divides by the run-time C on purpose: the
-    // shift form lets the scheduler interleave these loads with the walk and
-    // the kernel then spills at its 128-register cap)
     const int F = Fc / C;
 
-    // per-pixel upstream gradient of the group's channels and D = g . out
-    float gch[CG];
-    float D = 0.0f;
+    __shared__ BwdRec s_ent[BWD_WAVES][BWD_SUB];
+    __shared__ float s_tp[2][BWD_WAVES][2][64];  // T product and P of a wave's quarter (two batches)
+    __shared__ float s_g[MFMA ? CG : 1][MFMA ? 65 : 1];  // g, rows padded
+    __shared__ float s_v[MFMA ? 1 : BWD_WAVES][MFMA ? 1 : BWD_SUB][MFMA ? 1 : CG];  // attribute rows of the queue
+    // gv of the queue from the matrix cores, replaced by the pixel weights w
+    __shared__ float s_w[MFMA ? BWD_WAVES : 1][MFMA ? BWD_SUB : 1][65];
+
+    const uint32_t stop = inside ? n_last[q * s_pix + pix] : 0u;
+    uint32_t nent = stop;  // the walk ends at the largest stop position
 #pragma unroll
-    for (int k = 0; k < CG; ++k) {
-        const int ch = cg * CG + k;
+    for (int o = 32; o > 0; o >>= 1) nent = max(nent, (uint32_t)__shfl_xor((int)nent, o, 64));
+    nent = __builtin_amdgcn_readfirstlane(nent);
+    if (nent == 0) return;
+
+    // dL/dout of the pixel's channel ch0 + k: the elementwise part (read, or
+    // formed from the output and the target) + the set's channel-mean term;
+    // and D = g . out
+    auto upstream = [&](int k, float& o) -> float {
+        const int ch = ch0 + min(k, nch - 1);
         const int f = ch / C, comp = ch - f * C;
         const size_t idx = (((size_t)set * F + f) * HW + pix) * C + comp;
-        const float mk = mean_term(ch);  // uniform
-        gch[k] = inside ? upstream(idx) + (MFMA ? 0.0f : mk) : 0.0f;
-        D += inside ? (MFMA ? gch[k] + mk : gch[k]) * out[idx] : 0.0f;
-    }
-    const uint32_t stop = inside ? n_last[q * s_pix + pix] : 0u;
-
-    // MFMA operands held for the whole kernel:
-    //  gB (attribute gradient, B = g[pixel][channel]): for K-step s the lane
-    //    holds g of pixel 4s + lane/16 of its wave, channel nb*16 + lane%16;
-    //  gT (gv = v . g per entry and pixel, B = g^T[channel][pixel]): for
-    //    K-step k and pixel block pb the lane holds g of pixel 16 pb + lane%16,
-    //    channel 4k + lane/16.
-    float gB[MFMA ? 16 : 1][NB];
-    float gT[MFMA ? 4 : 1][MFMA ? CG / 4 : 1];
+        o = out[idx];
+        const float g = (tgt ? gscale * (o - tgt[idx]) : dout[idx]) + (mgrad ? mgrad[(size_t)set * Fc + ch] : 0.0f);
+        return inside && k < nch ? g : 0.0f;
+    };
+    float gch[MFMA ? 1 : CG];
+    float D = 0.0f;
     if constexpr (MFMA) {
-        // (t % tw and t / tw are computed directly: stepping them in loops
-        // puts a branch between the loads and serialises their latency)
+        // each wave a quarter of the channels, shared through LDS
+        constexpr int CW = CG / BWD_WAVES;
+        float gk[CW], ok[CW];
 #pragma unroll
-        for (int pb = 0; pb < 4; ++pb) {
-            const int t = wave * 64 + 16 * pb + (lane & 15);
-            const int pc = txi * tw + t % tw, pr = tyi * th + t / tw;
-            const bool in = t < nthr && pc < W && pr < H;
-            const size_t pp = in ? (size_t)pr * W + pc : 0;
+        for (int k = 0; k < CW; ++k) gk[k] = upstream(wave * CW + k, ok[k]);
 #pragma unroll
-            for (int k = 0; k < CG / 4; ++k) {
-                const int ch = cg * CG + 4 * k + (lane >> 4);
-                const int f = ch / C, comp = ch - f * C;
-                gT[pb][k] = in ? upstream((((size_t)set * F + f) * HW + pp) * C + comp) : 0.0f;
-            }
+        for (int k = 0; k < CW; ++k) {
+            s_g[wave * CW + k][lane] = gk[k];
+            D += inside && wave * CW + k < nch ? gk[k] * ok[k] : 0.0f;
         }
+        s_tp[0][wave][0][lane] = D;
+        __syncthreads();
+        D = 0.0f;
 #pragma unroll
-        for (int st = 0; st < 16; ++st) {
-            const int t = wave * 64 + 4 * st + (lane >> 4);
-            const int pc = txi * tw + t % tw, pr = tyi * th + t / tw;
-            const bool in = t < nthr && pc < W && pr < H;
-            const size_t pp = in ? (size_t)pr * W + pc : 0;
+        for (int w = 0; w < BWD_WAVES; ++w) D += s_tp[0][w][0][lane];
+    } else {
+        float ok[CG];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int ch = cg * CG + nb * 16 + (lane & 15);
-                const int f = ch / C, comp = ch - f * C;
-                gB[st][nb] = in ? upstream((((size_t)set * F + f) * HW + pp) * C + comp) : 0.0f;
-            }
-        }
+        for (int k = 0; k < CG; ++k) gch[k] = upstream(k, ok[k]);
+#pragma unroll
+        for (int k = 0; k < CG; ++k) D += inside && k < nch ? gch[k] * ok[k] : 0.0f;
     }
 
-    __shared__ double s_px[BWD_BATCH], s_py[BWD_BATCH], s_ca[BWD_BATCH], s_cb[BWD_BATCH], s_cc[BWD_BATCH];
-    __shared__ float s_sig[BWD_BATCH], s_att[BWD_BATCH];
-    __shared__ float s_caf[BWD_BATCH], s_cbf[BWD_BATCH], s_ccf[BWD_BATCH];
-    __shared__ uint32_t s_g[BWD_BATCH];
-    // per-entry sums over the workgroup's pixels, flushed once per batch
-    __shared__ float s_ad[BWD_BATCH][CG];
-    __shared__ float s_geo[BWD_BATCH][8];
-    __shared__ float s_m[CG];              // m_f of the group's channels
-    __shared__ float s_mvb[BWD_BATCH];     // sum_f m_f v_{e,f} per staged entry
-    // per wave, for the current run of entries: gv = v . g from the matrix
-    // cores, replaced entry by entry by the pixel weight w (rows padded)
-    __shared__ float s_w[MFMA ? 4 : 1][MFMA ? BWD_SUB : 1][65];
-
-    float T = 1.0f, P = 0.0f;
-    // the walk of this workgroup ends at the largest stop position of its pixels
-    __shared__ uint32_t s_maxstop;
-    if (threadIdx.x == 0) s_maxstop = 0;
-    if ((int)threadIdx.x < CG) s_m[threadIdx.x] = mean_term(cg * CG + threadIdx.x);
-    __syncthreads();
-    if (stop) atomicMax(&s_maxstop, stop);
-    __syncthreads();
-    const uint32_t end = rg.x + s_maxstop;
-    // a wave stops walking at the largest stop position of its own pixels
-    uint32_t wstop = stop;
+    float T = 1.0f, P = 0.0f;  // in front of the batch
+    uint32_t gn = 0;
+    GRec rn{};
+    auto fetch = [&](uint32_t b0) {
+        const uint32_t i = b0 + lane;
+        gn = i < nent ? plist[i] : gn;
+        rn = rec[gn];
+    };
+    gn = plist[0];
+    fetch(0);
+    int buf = 1;
+    for (uint32_t b0 = 0; b0 < nent; b0 += WALK_BATCH, buf ^= 1) {
+        // the wave's quarter of the entries that reach the pixels
+        const GRec r = rn;
+        const uint32_t g = gn;
+        bool pl;
+        const bool keep = box_reached(r, box, W, amin, pl) && b0 + lane < nent;
+        const unsigned long long km = __ballot(keep);
+        const bool plain = __ballot(keep && !pl) == 0ull;
+        const int n = __popcll(km);
+        const int per = ((n + BWD_WAVES - 1) / BWD_WAVES + BWD_STEP - 1) / BWD_STEP * BWD_STEP;
+        const int n0 = min(n, wave * per), cnt = min(n, n0 + per) - n0;  // uniform
+        const int slot = __popcll(km & ((1ull << lane) - 1ull)) - n0;
+        if (keep && slot >= 0 && slot < cnt) {
+            s_ent[wave][slot] = BwdRec{r.px, r.py, r.ca, 2.0 * r.cb, r.cc, r.sigma, r.att, (float)r.ca, (float)r.cb,
+                                       (float)r.cc, b0 + lane, g};
+            if constexpr (!MFMA) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) wstop = max(wstop, (uint32_t)__shfl_xor((int)wstop, o, 64));
-    const uint32_t wend = rg.x + wstop;
-    constexpr int shA = CG >= 64 ? 0 : (CG == 32 ? 1 : (CG == 16 ? 2 : (CG == 8 ? 3 : (CG == 4 ? 4 : (CG == 2 ? 5 : 6)))));
-
-    for (uint32_t b0 = rg.x; b0 < end; b0 += BWD_BATCH) {
-        __syncthreads();
-        const uint32_t i = b0 + threadIdx.x;
-        if (threadIdx.x < BWD_BATCH && i < end) {
-            const uint32_t g = plist[i];
-            const GRec r = rec[g];
-            s_px[threadIdx.x] = r.px;
-            s_py[threadIdx.x] = r.py;
-            s_ca[threadIdx.x] = r.ca;
-            s_cb[threadIdx.x] = r.cb;
-            s_cc[threadIdx.x] = r.cc;
-            s_caf[threadIdx.x] = (float)r.ca;
-            s_cbf[threadIdx.x] = (float)r.cb;
-            s_ccf[threadIdx.x] = (float)r.cc;
-            s_sig[threadIdx.x] = r.sigma;
-            s_att[threadIdx.x] = r.att;
-            s_g[threadIdx.x] = g;
-        }
-        for (int e = threadIdx.x; e < BWD_BATCH * CG; e += nthr) s_ad[e / CG][e % CG] = 0.0f;
-        for (int e = threadIdx.x; e < BWD_BATCH * 8; e += nthr) s_geo[e / 8][e % 8] = 0.0f;
-        __syncthreads();
-        const int m = (int)min((uint32_t)BWD_BATCH, end - b0);
-        if constexpr (MFMA) {
-            // sum_f m_f v_{e,f} of the staged entries: four threads per entry
-            const int e = threadIdx.x >> 2, qd = threadIdx.x & 3;
-            float mv = 0.0f;
-            if (e < m) {
-                const float* vr = A + (size_t)s_g[e] * Fc + qd * (CG / 4);
-#pragma unroll
-                for (int k = 0; k < CG / 4; ++k) mv = fmaf(s_m[qd * (CG / 4) + k], vr[k], mv);
+                for (int k = 0; k < CG; ++k) s_v[wave][slot][k] = k < nch ? A[(size_t)g * Fc + k] : 0.0f;
             }
-            mv += __shfl_xor(mv, 1, 64);
-            mv += __shfl_xor(mv, 2, 64);
-            if (qd == 0 && e < m) s_mvb[e] = mv;
-            __syncthreads();
         }
-        for (int j0 = 0; j0 < m; j0 += (MFMA ? BWD_SUB : m)) {
-            if (b0 + j0 >= wend) break;  // wave-uniform: nothing left for this wave
-            const int jn = MFMA ? min(BWD_SUB, m - j0) : m;
-            if constexpr (MFMA) {
-                // gv[e][p] = sum_f v[e][f] g[p][f]: A = v rows of the run
-                // (lane: entry lane%16, channel 4k + lane/16), B = gT
+        walk_wave_sync();
+        if (b0 + WALK_BATCH < nent) fetch(b0 + WALK_BATCH);
+        if constexpr (MFMA) {
+            if (cnt > 0) {
+                // gv[e][p] = sum_f v[e][f] g[p][f]: A = v rows (lane: entry
+                // lane % 16, channel 4k + lane / 16), B = g^T (channel
+                // 4k + lane / 16, pixel 16 pb + lane % 16)
                 const int e = lane & 15;
-                const bool ev = e < jn;
-                const CFloatB* vr = (const CFloatB*)(A + (size_t)(ev ? s_g[j0 + e] : 0u) * Fc) + (lane >> 4);
+                const bool ev = e < cnt;
+                const float* vr = A + (size_t)s_ent[wave][ev ? e : 0].g * Fc + (lane >> 4);
                 float va[CG / 4];
 #pragma unroll
-                for (int k = 0; k < CG / 4; ++k) va[k] = ev ? vr[4 * k] : 0.0f;
-
+                for (int k = 0; k < CG / 4; ++k) va[k] = ev && 4 * k + (lane >> 4) < nch ? vr[4 * k] : 0.0f;
                 f32x4 gv4[4];
 #pragma unroll
-                for (int pb = 0; pb < 4; ++pb) {
-                    gv4[pb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int pb = 0; pb < 4; ++pb) gv4[pb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                    for (int k = 0; k < CG / 4; ++k)
-                        gv4[pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[k], gT[pb][k], gv4[pb], 0, 0, 0);
-                }
-                // lane holds entries 4*(lane/16) + r of pixel 16 pb + lane%16
+                for (int k = 0; k < CG / 4; ++k)
+#pragma unroll
+                    for (int pb = 0; pb < 4; ++pb)
+                        gv4[pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            va[k], s_g[4 * k + (lane >> 4)][16 * pb + (lane & 15)], gv4[pb], 0, 0, 0);
+                // lane holds entries 4 (lane / 16) + r of pixel 16 pb + lane % 16
 #pragma unroll
                 for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) s_w[wave][4 * (lane >> 4) + r][16 * pb + (lane & 15)] = gv4[pb][r];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    for (int rr = 0; rr < 4; ++rr) s_w[wave][4 * (lane >> 4) + rr][16 * pb + (lane & 15)] = gv4[pb][rr];
+                walk_wave_sync();
             }
-            for (int jj = 0; jj < (MFMA ? BWD_SUB : jn); ++jj) {
-                const int j = j0 + jj;
-                float w = 0.0f;
-                if (jj < jn && b0 + j < wend) {
-                    double dx = pcx - s_px[j];
-                    dx += dx >= halfW ? -(double)W : (dx < -halfW ? (double)W : 0.0);
-                    const double dy = pcy - s_py[j];
-                    const double ca = s_ca[j], cb = s_cb[j], cc = s_cc[j];
-                    const double qv = ca * dx * dx + 2.0 * cb * dx * dy + cc * dy * dy;
-                    const float G = __builtin_amdgcn_exp2f((float)(-0.5 * LOG2E_B * qv));
-                    const float sig = s_sig[j], att = s_att[j];
-                    const float sg = sig * G;
-                    const float alpha = fminf(amax, sg);
-                    const bool take = (b0 + j - rg.x) < stop && alpha >= amin;
-                    if (__ballot(take) != 0ull) {  // else the whole wave skips the entry
-                        float gv = 0.0f;
-                        if constexpr (MFMA) {
-                            gv = s_w[wave][jj][lane] + s_mvb[j];
-                        } else {
-                            const uint32_t g = __builtin_amdgcn_readfirstlane(s_g[j]);
-                            const float* vp = A + (size_t)g * Fc;
+        }
+        auto value = [&](int e) -> float {  // v . g of queue entry e
+            if constexpr (MFMA) return s_w[wave][e][lane];
+            float gv = 0.0f;
 #pragma unroll
-                            for (int k = 0; k < CG; ++k) gv = fmaf(gch[k], vp[k], gv);
-                        }
-                        // branch-free: a lane that does not take the entry
-                        // gets Ta = 0, so every term below is zero and T, P
-                        // stay as they are
-                        const float cA = att * gv;
-                        const float Ta = take ? T * alpha : 0.0f;
-                        const float Pn = P + Ta * cA;
-                        // alpha <= alpha_max < 1; a one-ulp reciprocal is ample here
-                        const float dalpha = T * cA - (D - Pn) * __builtin_amdgcn_rcpf(1.0f - alpha);
-                        const float dsg = (take && sg < amax) ? dalpha : 0.0f;  // clamp passes nothing
-                        const float dq = -0.5f * dsg * sig * G;
-                        w = Ta * att;
-                        // gradient factors in FP32 from the exact offsets
-                        const float dxf = (float)dx, dyf = (float)dy;
-                        const float dq2 = -2.0f * dq;
-                        float geo[8];
-                        geo[0] = dq2 * fmaf(s_caf[j], dxf, s_cbf[j] * dyf);  // d/dpx
-                        geo[1] = dq2 * fmaf(s_cbf[j], dxf, s_ccf[j] * dyf);  // d/dpy
-                        geo[2] = dq * (dxf * dxf);                           // d/dA
-                        geo[3] = dq * (2.0f * dxf * dyf);                    // d/dB
-                        geo[4] = dq * (dyf * dyf);                           // d/dC
-                        geo[5] = dsg * G;                                   // d/dsigma
-                        geo[6] = Ta * gv;                                   // d/da
-                        geo[7] = w;                                         // sum_p w (mean term)
-                        T = take ? T * (1.0f - alpha) : T;
-                        P = Pn;
-                        wave_reduce_scatter8(geo, lane);
-                        if ((lane & 7) == 0) atomicAdd(&s_geo[j][lane >> 3], geo[0]);
-                        if constexpr (!MFMA) {
-                            float red[CG];
+            for (int k = 0; k < (MFMA ? 1 : CG); ++k) gv = fmaf(gch[k], s_v[wave][e][k], gv);
+            return gv;
+        };
+        auto offset = [&](const BwdRec& br, double& dx, double& dy) {
+            dx = pcx - br.px;
+            if (!plain) dx += dx >= halfW ? -(double)W : (dx < -halfW ? (double)W : 0.0);
+            dy = pcy - br.py;
+        };
+        // G where the pixel takes the entry, else -1, and the quarter's T and P
+        float G[BWD_SUB], Tl = 1.0f, Pl = 0.0f;
 #pragma unroll
-                            for (int k = 0; k < CG; ++k) red[k] = w * gch[k];
-                            wave_reduce_scatter<CG>(red, lane);
-                            if ((lane & ((1 << shA) - 1)) == 0) atomicAdd(&s_ad[j][lane >> shA], red[0]);
-                        }
-                    }
+        for (int j = 0; j < BWD_SUB; j += BWD_STEP) {
+            if (j >= cnt) break;
+            float al[BWD_STEP], cA[BWD_STEP];
+#pragma unroll
+            for (int i = 0; i < BWD_STEP; ++i) {
+                const int e = min(j + i, cnt - 1);
+                const BwdRec& br = s_ent[wave][e];
+                double dx, dy;
+                offset(br, dx, dy);
+                const double qv = br.ca * dx * dx + br.cb2 * dx * dy + br.cc * dy * dy;
+                const float Gv = __builtin_amdgcn_exp2f((float)(-0.5 * WALK_LOG2E * qv));
+                al[i] = fminf(amax, br.sigma * Gv);
+                const bool take = j + i < cnt && br.pos < stop && al[i] >= amin;
+                G[j + i] = take ? Gv : -1.0f;
+                al[i] = take ? al[i] : 0.0f;
+                cA[i] = br.att * value(e);
+            }
+#pragma unroll
+            for (int i = 0; i < BWD_STEP; ++i) {
+                Pl += Tl * al[i] * cA[i];
+                Tl *= 1.0f - al[i];
+            }
+        }
+        s_tp[buf][wave][0][lane] = Tl;
+        s_tp[buf][wave][1][lane] = Pl;
+        __syncthreads();
+        float Te = T, Pe = P;  // in front of the quarter
+#pragma unroll
+        for (int w = 0; w < BWD_WAVES; ++w) {
+            if (w == wave) {
+                Te = T;
+                Pe = P;
+            }
+            P += T * s_tp[buf][w][1][lane];
+            T *= s_tp[buf][w][0][lane];
+        }
+        // the terms, entry by entry; a pixel that does not take an entry gets
+        // Ta = 0, so every term is zero and T, P stay
+#pragma unroll
+        for (int j = 0; j < BWD_SUB; j += BWD_STEP) {
+            if (j >= cnt) break;
+            float geo[BWD_STEP][8], wt[BWD_STEP];
+#pragma unroll
+            for (int i = 0; i < BWD_STEP; ++i) {
+                const int e = min(j + i, cnt - 1);
+                const BwdRec& br = s_ent[wave][e];
+                double dx, dy;
+                offset(br, dx, dy);
+                const float dxf = (float)dx, dyf = (float)dy, gv = value(e);
+                const bool take = !(G[j + i] < 0.0f);
+                const float Gv = take ? G[j + i] : 0.0f;
+                const float sg = br.sigma * Gv;
+                const float al = take ? fminf(amax, sg) : 0.0f;
+                const float cA = br.att * gv;
+                const float Ta = Te * al;
+                Pe += Ta * cA;
+                // alpha <= alpha_max < 1; a one-ulp reciprocal is ample here
+                const float dalpha = Te * cA - (D - Pe) * __builtin_amdgcn_rcpf(1.0f - al);
+                const float dsg = (take && sg < amax) ? dalpha : 0.0f;  // clamp passes nothing
+                const float dq = -0.5f * dsg * br.sigma * Gv;
+                const float w = Ta * br.att;
+                // gradient factors in FP32 from the exact offsets
+                const float dq2 = -2.0f * dq;
+                geo[i][0] = dq2 * fmaf(br.caf, dxf, br.cbf * dyf);  // d/dpx
+                geo[i][1] = dq2 * fmaf(br.cbf, dxf, br.ccf * dyf);  // d/dpy
+                geo[i][2] = dq * (dxf * dxf);                       // d/dA
+                geo[i][3] = dq * (2.0f * dxf * dyf);                // d/dB
+                geo[i][4] = dq * (dyf * dyf);                       // d/dC
+                geo[i][5] = dsg * Gv;                               // d/dsigma
+                geo[i][6] = Ta * gv;                                // d/da
+                geo[i][7] = CG == 1 ? w * gch[0] : 0.0f;            // d/dv of the only channel
+                wt[i] = w;
+                Te *= 1.0f - al;
+            }
+            // the sums over the wave: 8 lanes end with each of an entry's 8
+            // terms, and the entries leave from different ones of them
+            bool any = false;
+#pragma unroll
+            for (int i = 0; i < BWD_STEP; ++i) {
+                if constexpr (MFMA)
+                    if (j + i < cnt) s_w[wave][j + i][lane] = wt[i];
+                any |= !(G[j + i] < 0.0f);
+            }
+            if (__ballot(any) == 0ull) continue;
+            const BwdRec& be = s_ent[wave][min(j + (lane & (BWD_STEP - 1)), cnt - 1)];
+            const uint32_t pos = be.pos;
+            float* const dv = dA + (size_t)be.g * Fc;
+            float v = 0.0f;
+#pragma unroll
+            for (int i = 0; i < BWD_STEP; ++i) {
+                wave_reduce_scatter8(geo[i], lane);
+                v = (lane & 7) == i ? geo[i][0] : v;
+            }
+            if (v != 0.0f) {
+                float* p = gacc + (size_t)pos * 8 + (lane >> 3);
+                if (CG == 1 && lane >= 56) p = dv;
+                unsafeAtomicAdd(p, v);
+            }
+            if constexpr (!MFMA && CG > 1) {
+                constexpr int shA = CG == 8 ? 3 : (CG == 4 ? 4 : 5);
+                v = 0.0f;
+#pragma unroll
+                for (int i = 0; i < BWD_STEP; ++i) {
+                    float red[CG];
+#pragma unroll
+                    for (int k = 0; k < CG; ++k) red[k] = wt[i] * gch[k];
+                    wave_reduce_scatter<CG>(red, lane);
+                    v = (lane & ((1 << shA) - 1)) == i ? red[0] : v;
                 }
-                if constexpr (MFMA) s_w[wave][jj][lane] = w;
+                if (v != 0.0f && (lane >> shA) < nch) unsafeAtomicAdd(dv + (lane >> shA), v);
             }
-            if constexpr (MFMA) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        if constexpr (MFMA) {
+            if (cnt > 0) {
+                // (rows behind cnt hold what the first product left; their
+                // sums are not used)
+                walk_wave_sync();
                 f32x4 acc[NB];
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -350,36 +387,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                     const float a = s_w[wave][lane & 15][4 * st + (lane >> 4)];
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, gB[st][nb], acc[nb], 0, 0, 0);
+                        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            a, s_g[16 * nb + (lane & 15)][4 * st + (lane >> 4)], acc[nb], 0, 0, 0);
                 }
-                // lane holds entries 4*(lane/16) + r, channel nb*16 + lane%16
+                // lane holds entries 4 (lane / 16) + r, channel 16 nb + lane % 16
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int e = 4 * (lane >> 4) + r;
-                    if (e < jn) {
+                for (int rr = 0; rr < 4; ++rr) {
+                    const int e = 4 * (lane >> 4) + rr;
+                    if (e < cnt) {
+                        float* p = dA + (size_t)s_ent[wave][e].g * Fc + (lane & 15);
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb)
-                            if (acc[nb][r] != 0.0f) atomicAdd(&s_ad[j0 + e][nb * 16 + (lane & 15)], acc[nb][r]);
+                            if (acc[nb][rr] != 0.0f && 16 * nb + (lane & 15) < nch) unsafeAtomicAdd(p + 16 * nb, acc[nb][rr]);
                     }
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             }
         }
-        __syncthreads();
-        // flush: attribute gradients (one atomic per entry and channel per
-        // workgroup), geometric terms into the per-pair accumulator
-        for (int e = threadIdx.x; e < m * CG; e += nthr) {
-            const int j = e / CG, k = e % CG;
-            const float val = MFMA ? s_ad[j][k] + s_m[k] * s_geo[j][7] : s_ad[j][k];
-            if (val != 0.0f) unsafeAtomicAdd(dA + (size_t)s_g[j] * Fc + k, val);
-        }
-        for (int e = threadIdx.x; e < m * 8; e += nthr) {
-            const int j = e / 8, k = e % 8;
-            const float val = k < 7 ? s_geo[j][k] : 0.0f;  // slot 7 holds sum_p w
-            if (val != 0.0f) unsafeAtomicAdd(gacc + (size_t)(b0 + j) * 8 + k, val);
-        }
+        walk_wave_sync();
     }
 }
 
@@ -933,11 +957,17 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
                            (float*)(ws + L.gacc), d_attr, a.query_stride, 0, (float*)nullptr);
         timing_end(tok, s);
     } else {
-    int cg = choose_chan_group(Fc, p.chan_group);
-    if (cg > 32) cg = 32;
-    if (Fc / cg > 65535) return GS_ERR_CAPACITY;
+    // the caller's group where it is valid; else the smallest
+    // power of two that holds every channel float, 64 at most and the last
+    // group partly filled: a walk per group costs more than empty channels
+    int cg = p.chan_group > 0 ? choose_chan_group(Fc, p.chan_group) : 1;
+    if (!(p.chan_group > 0 && cg == p.chan_group))
+        for (cg = 1; cg < 64 && cg < Fc;) cg *= 2;
+    if (cg > 64) cg = 64;
+    const int ngr = (Fc + cg - 1) / cg;
+    if (ngr > 65535) return GS_ERR_CAPACITY;
     const int shared = (L.nq == 1 && n_sets > 1) ? 1 : 0;
-    dim3 grid(L.T, Fc / cg, n_sets), block(L.tw * L.th);
+    dim3 grid(L.T * ((L.tw * L.th) >> 6), ngr, n_sets), block(64 * BWD_WAVES);
     const int64_t das = a.query_stride;  // d_attr mirrors the attribute layout
     void* tok;
     timing_begin(TK_BLEND_BWD, s, &tok);
@@ -947,7 +977,8 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
         case 4: bwd_cg<4>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
         case 8: bwd_cg<8>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
         case 16: bwd_cg<16>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
-        default: bwd_cg<32>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
+        case 32: bwd_cg<32>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
+        default: bwd_cg<64>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
     }
     timing_end(tok, s);
     }
