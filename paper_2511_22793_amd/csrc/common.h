@@ -111,9 +111,6 @@ constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;  // keys per sort workgroup
 // at least SORT_WIDE_MIN_BLOCKS workgroups.
 constexpr int SORT_WIDE_WAVES = 16;
 constexpr int SORT_WIDE_MIN_BLOCKS = 256;
-// at most this many blocks per query: the depth sort's scatter scans the
-// per-block counts itself instead of a separate scan launch
-constexpr int SORT_FUSED_SCAN_BLOCKS = 64;
 constexpr int RADIX_BITS = 8;
 constexpr int RADIX = 1 << RADIX_BITS;
 // tile ids up to this many bits are sorted in one counting pass
@@ -179,6 +176,7 @@ void launch_fill_dev(uint32_t* p, size_t max_count, size_t q_stride, int nq, con
                      uint32_t per_query, hipStream_t s);
 void launch_project(const gs_scene& sc, const gs_queries& qs, const gs_grid& g, const gs_params& p,
                     const Layout& L, char* ws, hipStream_t s);
+size_t depth_keys_in(const Layout& L);  // where the depth sort reads its keys (offset of the query array)
 void launch_depth_sort(const Layout& L, char* ws, hipStream_t s);
 void launch_binning(const Layout& L, char* ws, hipStream_t s);
 gs_status launch_blend(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out,

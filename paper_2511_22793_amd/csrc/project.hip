@@ -200,7 +200,7 @@ void launch_project(const gs_scene& sc, const gs_queries& qs, const gs_grid& g, 
                        p.r_near, (double)p.dilation, (double)p.atten_power, p.atten_ref, (double)p.margin,
                        (GRec*)(ws + L.rec), L.s_rec / sizeof(GRec), (int4*)(ws + L.rect), L.s_rect / sizeof(int4),
                        (uint32_t*)(ws + L.status), L.s_status / 4, (uint4*)(ws + L.tinfo),
-                       L.s_tinfo / sizeof(uint4), (uint32_t*)(ws + L.keys_a), (uint32_t*)(ws + L.vals_a),
+                       L.s_tinfo / sizeof(uint4), (uint32_t*)(ws + depth_keys_in(L)), (uint32_t*)(ws + L.vals_a),
                        L.s_keys / 4, (uint32_t*)(ws + L.flags), L.s_flags / 4);
 }
 

@@ -2,8 +2,10 @@
 // Gaussians are binned to tiles and each tile's list is ordered by distance
 // to the receiver, Sec. 4.2 and the per-pixel loop of Algorithm 1).
 //
-// 1. depth sort: stable LSD radix sort of the FP32 distance keys (index
-//    order breaks ties), 8-bit digits, one pass = count + scan + scatter;
+// 1. depth sort of the FP32 distance keys, index order breaking ties: by
+//    ranking, or by sampled splitters into bins that each fit a workgroup;
+//    beyond half a million keys a stable LSD radix sort (8-bit digits, one pass =
+//    count + scan + scatter);
 // 2. tiles-touched scan: exclusive prefix sum of the tile counts in depth
 //    order, giving each Gaussian's first pair slot and the pair total;
 // 3. pair emission: key = tile << rank_bits | depth_rank, unique per pair;
@@ -71,9 +73,8 @@ __device__ __forceinline__ uint32_t seg_count(const uint32_t* n_dev, size_t n_st
 }
 
 // Per-workgroup digit histogram (RB-bit digits) of a block of 64*WV*IT
-// keys; counts laid out [digit][block] per query, or [block][digit] (BM)
-// for the scatter that scans them itself.
-template <int RB, int IT = SORT_ITEMS, int WV = SORT_THREADS / 64, bool BM = false>
+// keys; counts laid out [digit][block] per query.
+template <int RB, int IT = SORT_ITEMS, int WV = SORT_THREADS / 64>
 __global__ __launch_bounds__(64 * WV) void k_sort_count(
     const uint32_t* __restrict__ keys, size_t s_keys, const uint32_t* __restrict__ n_dev, size_t n_stride,
     uint32_t n_fixed, int shift, uint32_t* __restrict__ counts, size_t s_counts, int max_blocks)
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(64 * WV) void k_sort_count(
     }
     __syncthreads();
     for (int d = threadIdx.x; d < R; d += NT)
-        counts[q * s_counts + (BM ? (size_t)blockIdx.x * R + d : (size_t)d * max_blocks + blockIdx.x)] = hist[d];
+        counts[q * s_counts + (size_t)d * max_blocks + blockIdx.x] = hist[d];
 }
 
 // Exclusive scan over blocks for one digit (one workgroup per digit and
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(256) void k_sort_scan(uint32_t* __restrict__ counts
 // below it with the same digit in this round, from an RB-ballot match mask).
 // With `order` set (the single tile pass over pair keys) the output is the
 // pair's Gaussian, order[key & rank_mask], instead of the key.
-template <int RB, int IT = SORT_ITEMS, bool KV = true, int WV = SORT_THREADS / 64, bool FS = false>
+template <int RB, int IT = SORT_ITEMS, bool KV = true, int WV = SORT_THREADS / 64>
 __global__ __launch_bounds__(64 * WV) void k_sort_scatter(
     const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
     uint32_t* __restrict__ vout, size_t s_keys, const uint32_t* __restrict__ n_dev, size_t n_stride,
@@ -181,39 +182,12 @@ __global__ __launch_bounds__(64 * WV) void k_sort_scatter(
         vout += q * s_keys;
     }
     // digit bases: exclusive scan of the totals over digits (thread tid <
-    // NDT owns digits [tid*DPT, tid*DPT + DPT)).  FS: the counts are
-    // [block][digit] and this workgroup forms its digits' totals and its
-    // earlier-block prefixes itself (no scan launch; for a few blocks).
+    // NDT owns digits [tid*DPT, tid*DPT + DPT)).
     {
         const bool own = tid < NDT;
         uint32_t t[DPT], tsum = 0;
-        uint32_t pre[FS ? DPT : 1];
-        if constexpr (FS) {
-            const int nb = (int)((n + TILE - 1) / TILE);
-            const uint32_t* cq = counts + q * s_counts + (size_t)tid * DPT;
 #pragma unroll
-            for (int k = 0; k < DPT; ++k) t[k] = pre[k] = 0u;
-            if (own) {
-                // eight blocks' loads in flight at a time
-                for (int b0 = 0; b0 < nb; b0 += 8) {
-                    uint32_t c[8][DPT];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-#pragma unroll
-                        for (int k = 0; k < DPT; ++k) c[u][k] = b0 + u < nb ? cq[(size_t)(b0 + u) * R + k] : 0u;
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-#pragma unroll
-                        for (int k = 0; k < DPT; ++k) {
-                            t[k] += c[u][k];
-                            pre[k] += b0 + u < (int)blockIdx.x ? c[u][k] : 0u;
-                        }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < DPT; ++k) t[k] = own ? totals[q * s_totals + tid * DPT + k] : 0u;
-        }
+        for (int k = 0; k < DPT; ++k) t[k] = own ? totals[q * s_totals + tid * DPT + k] : 0u;
 #pragma unroll
         for (int k = 0; k < DPT; ++k) tsum += t[k];
         uint32_t x = tsum;
@@ -231,10 +205,7 @@ __global__ __launch_bounds__(64 * WV) void k_sort_scatter(
 #pragma unroll
             for (int k = 0; k < DPT; ++k) {
                 const int d = tid * DPT + k;
-                if constexpr (FS)
-                    s_goff[d] = run + pre[k];
-                else
-                    s_goff[d] = run + counts[q * s_counts + (size_t)d * max_blocks + blockIdx.x];
+                s_goff[d] = run + counts[q * s_counts + (size_t)d * max_blocks + blockIdx.x];
                 // the tile pass: [start, end) of tile d is its digit range
                 if (ranges && blockIdx.x == 0 && d < T) ranges[q * s_ranges + d] = make_uint2(run, run + t[k]);
                 run += t[k];
@@ -320,16 +291,6 @@ static void sort_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, 
     uint32_t* counts = (uint32_t*)(ws + L.counts);
     uint32_t* totals = (uint32_t*)(ws + L.totals);
     const size_t sc = L.s_counts / 4, st = L.s_totals / 4;
-    if (!n_dev && blocks <= SORT_FUSED_SCAN_BLOCKS) {
-        // a fixed key count (the depth sort) in a few blocks: the scatter
-        // scans the block-major counts itself (the digit totals are not kept)
-        hipLaunchKernelGGL((k_sort_count<RB, IT, WV, true>), dim3(blocks, L.nq), dim3(64 * WV), 0, s, kin, s_keys,
-                           n_dev, n_stride, n_fixed, shift, counts, sc, blocks);
-        hipLaunchKernelGGL((k_sort_scatter<RB, IT, KV, WV, true>), dim3(blocks, L.nq), dim3(64 * WV), 0, s, kin, vin,
-                           kout, vout, s_keys, n_dev, n_stride, n_fixed, shift, counts, sc, totals, st, blocks,
-                           order, s_order, plist, s_plist, rank_mask, (uint2*)nullptr, (size_t)0, 0);
-        return;
-    }
     hipLaunchKernelGGL((k_sort_count<RB, IT, WV>), dim3(blocks, L.nq), dim3(64 * WV), 0, s, kin, s_keys, n_dev,
                        n_stride, n_fixed, shift, counts, sc, blocks);
     hipLaunchKernelGGL(k_sort_scan, dim3(1 << RB, L.nq), dim3(256), 0, s, counts, sc, totals, st, n_dev, n_stride,
@@ -362,22 +323,6 @@ static int radix_sort(uint32_t* ka, uint32_t* kb, uint32_t* va, uint32_t* vb, si
     return passes & 1;
 }
 
-void launch_depth_sort(const Layout& L, char* ws, hipStream_t s)
-{
-    // keys a -> ... -> a after 4 passes (even), values follow
-    radix_sort((uint32_t*)(ws + L.keys_a), (uint32_t*)(ws + L.keys_b), (uint32_t*)(ws + L.vals_a),
-               (uint32_t*)(ws + L.vals_b), L.s_keys / 4, nullptr, 0, (uint32_t)L.n, 0, 4, L.sort_blocks,
-               L.sort_wide != 0, L, ws, s);
-}
-
-// ---- tiles-touched scan and pair emission -------------------------------
-// Scan granularity: EMIT_RANKS consecutive depth ranks per workgroup.
-constexpr int EMIT_RANKS = 64;
-// up to this many blocks the emission adds up the block sums itself (each
-// workgroup reads the sums before its own: quadratic, so only for a few
-// thousand blocks)
-constexpr int EMIT_SCAN_BLOCKS = 2048;
-
 // Exclusive scan within a 256-thread workgroup; returns the prefix of v.
 __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_t* wsum)
 {
@@ -394,6 +339,415 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_
     for (int k = 0; k < w; ++k) base += wsum[k];
     return base + x - v;
 }
+
+// ---- depth sort ----------------------------------------------------------
+// Elements are (key, index) pairs compared as one 64-bit number, so equal
+// keys stay in index order and no stage has to be stable.
+//
+// Up to DS_ONE keys: every key is ranked against all others.
+// Up to DS_MAX keys: 4 keys per bin, at jittered places, are ranked against
+// each other and every fourth becomes a splitter; each key finds its bin by
+// binary search and takes a place in it (one atomic per workgroup and bin);
+// the keys move to their bins; a workgroup per bin sorts it.  Four launches
+// and two passes over the keys where the radix sort has 8 to 12 and four; at
+// these sizes the launches and their latency are the time (2,000 keys: 35 us
+// in 8 launches by the radix sort, 6 us so; 100,000: 48 and 28 us; 300,000:
+// 64 us in 12 launches and 40 us).
+// Beyond DS_MAX the 1024 bins (512 keys on average there, a largest of 4 times
+// that with 4 samples per bin) outgrow a workgroup's registers.  A bin that
+// the samples missed and that does not fit (the places are known, so one can
+// be built) is sorted in place in global memory by its workgroup: slow, but
+// right.
+constexpr int DS_ONE = 4096;
+constexpr int DS_MAX = 1 << 19;
+constexpr int DS_MAX_BINS = 1024; // words of a query's totals
+constexpr int DS_BIN = 320;       // keys per bin aimed at
+constexpr int DS_OVER = 4;        // samples per bin
+constexpr int DS_RANK = 32;       // elements ranked per workgroup
+constexpr int DS_WAVES = 4;       // waves that sort a bin, 2, 4 or 8 keys per thread
+constexpr int DS_CAP = 64 * 8 * DS_WAVES;
+
+static int depth_bins(int n)
+{
+    int b = 16;
+    while (b < DS_MAX_BINS && n / b > DS_BIN) b *= 2;
+    return b;
+}
+
+typedef unsigned long long DsKey;
+
+// x of lane ^ m, by DPP and permlane swaps (the LDS crossbar of __shfl_xor
+// made the sorts below 1.4 times slower); m a constant after unrolling.
+template <int CTRL>
+__device__ __forceinline__ uint32_t lane_dpp(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+
+__device__ __forceinline__ uint32_t lane_swap16(uint32_t x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return threadIdx.x & 16 ? r[0] : r[1];
+}
+
+__device__ __forceinline__ uint32_t lane_swap32(uint32_t x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return threadIdx.x & 32 ? r[0] : r[1];
+}
+
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x)
+{
+    constexpr int Q1 = 0xB1, Q2 = 0x4E, Q3 = 0x1B;      // quad_perm: lane ^ 1, 2, 3
+    constexpr int M7 = 0x141, R8 = 0x128, M15 = 0x140;  // row_half_mirror, row_ror:8, row_mirror
+    if constexpr (M == 1) return lane_dpp<Q1>(x);
+    if constexpr (M == 2) return lane_dpp<Q2>(x);
+    if constexpr (M == 3) return lane_dpp<Q3>(x);
+    if constexpr (M == 4) return lane_dpp<Q3>(lane_dpp<M7>(x));
+    if constexpr (M == 7) return lane_dpp<M7>(x);
+    if constexpr (M == 8) return lane_dpp<R8>(x);
+    if constexpr (M == 15) return lane_dpp<M15>(x);
+    if constexpr (M == 16) return lane_swap16(x);
+    if constexpr (M == 31) return lane_swap16(lane_dpp<M15>(x));
+    if constexpr (M == 32) return lane_swap32(x);
+    if constexpr (M == 63) return lane_swap32(lane_swap16(lane_dpp<M15>(x)));
+    return x;
+}
+
+// Sorts 64 NW E elements held E per thread by 64 NW threads, ascending:
+// element E tid + i ends in v[i] of thread tid.  A bitonic network whose
+// comparators all point upwards (the first stage of each merge mirrors):
+// inside a thread by registers, between lanes by lane permutations, between
+// waves through LDS (x: 64 NW E elements).
+template <int NW, int E, int K, int J>
+__device__ __forceinline__ void sort_stage(DsKey* v, int tid, DsKey* x)
+{
+    constexpr int NT = 64 * NW;
+    constexpr bool mirror = J == K / 2;
+    if constexpr (J < E) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const int o = i ^ (mirror ? K - 1 : J);
+            if (o > i) {
+                const DsKey a = v[i], b = v[o];
+                const bool sw = a > b;
+                v[i] = sw ? b : a;
+                v[o] = sw ? a : b;
+            }
+        }
+    } else {
+        constexpr int tm = mirror ? K / E - 1 : J / E, rm = mirror ? E - 1 : 0;
+        const bool low = (tid & (J / E)) == 0;
+        DsKey p[E];
+        if constexpr (tm < 64) {
+#pragma unroll
+            for (int i = 0; i < E; ++i)
+                p[i] = ((DsKey)lane_xor<tm>((uint32_t)(v[i ^ rm] >> 32)) << 32) | lane_xor<tm>((uint32_t)v[i ^ rm]);
+        } else {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < E; ++i) x[i * NT + tid] = v[i];
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < E; ++i) p[i] = x[(i ^ rm) * NT + (tid ^ tm)];
+        }
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[i] = (p[i] < v[i]) == low ? p[i] : v[i];
+    }
+    if constexpr (J > 1)
+        sort_stage<NW, E, K, J / 2>(v, tid, x);
+    else if constexpr (K < E * NT)
+        sort_stage<NW, E, 2 * K, K>(v, tid, x);
+}
+
+template <int NW, int E>
+__device__ __forceinline__ void sort_regs(DsKey* v, int tid, DsKey* x)
+{
+    sort_stage<NW, E, 2, 1>(v, tid, x);
+}
+
+// m elements from (keys, vals) to (kout, vout), which may be the same arrays:
+// everything is read before anything is written.
+template <int NW, int E>
+__device__ __forceinline__ void sort_run(const uint32_t* keys, const uint32_t* vals, uint32_t* kout, uint32_t* vout,
+                                         uint32_t m, int tid, DsKey* x)
+{
+    DsKey v[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const uint32_t e = i * 64 * NW + tid;
+        v[i] = e < m ? ((DsKey)keys[e] << 32) | vals[e] : ~0ull;
+    }
+    sort_regs<NW, E>(v, tid, x);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const uint32_t e = tid * E + i;
+        if (e < m) {
+            kout[e] = (uint32_t)(v[i] >> 32);
+            vout[e] = (uint32_t)v[i];
+        }
+    }
+}
+
+// Ranks DS_RANK elements per workgroup against M of them (8 threads per
+// element, an eighth of the M each).  ALL: the M = n elements are the keys
+// themselves, which go straight to their ranks: the whole sort.  Else they
+// are M = DS_OVER B samples, the one of rank DS_OVER k becomes split[k], and
+// workgroup 0 clears the bins' counts.
+template <bool ALL>
+__global__ __launch_bounds__(256) void k_depth_rank(const uint32_t* __restrict__ keys, size_t s_keys, uint32_t n,
+                                                    int M, DsKey* __restrict__ split, size_t s_split,
+                                                    uint32_t* __restrict__ tot, size_t s_tot,
+                                                    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout)
+{
+    const int q = blockIdx.y;
+    __shared__ alignas(16) DsKey v[DS_ONE];
+    __shared__ uint32_t s_rank[DS_RANK];
+    static_assert(DS_OVER * DS_MAX_BINS <= DS_ONE, "depth sort");
+    keys += q * s_keys;
+    const int log_m = 31 - __clz(M);
+    const uint32_t step = n >> log_m;
+    const int Mp = (M + 15) & ~15;  // padded: whole pairs per eighth
+    constexpr int UN = DS_ONE / 256;
+    uint32_t e[UN], kv[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+        const int i = u * 256 + threadIdx.x;
+        e[u] = i;
+        // (M, a power of two, divides by a shift)
+        if constexpr (!ALL)
+            e[u] = (uint32_t)(((uint64_t)i * n) >> log_m) + __umulhi((uint32_t)i * 0x9E3779B1u, step);
+        kv[u] = i < M ? keys[e[u]] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+        const int i = u * 256 + threadIdx.x;
+        if (i < Mp) v[i] = i < M ? ((DsKey)kv[u] << 32) | e[u] : ~0ull;
+    }
+    if (threadIdx.x < DS_RANK) s_rank[threadIdx.x] = 0u;
+    if (!ALL && blockIdx.x == 0)
+        for (int b = threadIdx.x; b < M / DS_OVER; b += 256) tot[q * s_tot + b] = 0u;
+    __syncthreads();
+    constexpr int SEG = 256 / DS_RANK;
+    const int sm = threadIdx.x % DS_RANK, seg = threadIdx.x / DS_RANK;
+    const int me = blockIdx.x * DS_RANK + sm;
+    const DsKey mine = me < M ? v[me] : ~0ull;
+    const int len = Mp / SEG / 2;
+    const ulonglong2* p = (const ulonglong2*)v + seg * len;
+    uint32_t r = 0u;
+#pragma unroll 8
+    for (int i = 0; i < len; ++i) {
+        const ulonglong2 c = p[i];
+        r += c.x < mine ? 1u : 0u;
+        r += c.y < mine ? 1u : 0u;
+    }
+    atomicAdd(&s_rank[sm], r);
+    __syncthreads();
+    if (threadIdx.x < DS_RANK && me < M) {
+        const uint32_t rank = s_rank[sm];
+        if constexpr (ALL) {
+            kout[q * s_keys + rank] = (uint32_t)(mine >> 32);
+            vout[q * s_keys + rank] = (uint32_t)mine;
+        } else if (rank % DS_OVER == 0) {
+            split[q * s_split + rank / DS_OVER] = mine;
+        }
+    }
+}
+
+// Each key's bin and its place there, packed: bin << 20 | place (places
+// are below n <= 2^19).  A bin's place counter is advanced once per workgroup.
+__global__ __launch_bounds__(SORT_THREADS) void k_depth_bin(const uint32_t* __restrict__ keys, size_t s_keys,
+                                                            uint32_t n, const DsKey* __restrict__ split,
+                                                            size_t s_split, int B, uint32_t* __restrict__ tot,
+                                                            size_t s_tot, uint32_t* __restrict__ packed)
+{
+    const int q = blockIdx.y;
+    __shared__ DsKey s_split_[DS_MAX_BINS];
+    __shared__ uint32_t s_cnt[DS_MAX_BINS];
+    keys += q * s_keys;
+    const uint32_t base = blockIdx.x * SORT_TILE + threadIdx.x;
+    uint32_t kv[SORT_ITEMS];
+#pragma unroll
+    for (int i = 0; i < SORT_ITEMS; ++i) {
+        const uint32_t e = base + i * SORT_THREADS;
+        kv[i] = e < n ? keys[e] : 0u;
+    }
+    for (int b = threadIdx.x; b < B; b += SORT_THREADS) {
+        s_split_[b] = split[q * s_split + b];
+        s_cnt[b] = 0u;
+    }
+    __syncthreads();
+    int bin[SORT_ITEMS];
+#pragma unroll
+    for (int i = 0; i < SORT_ITEMS; ++i) bin[i] = 0;
+    for (int st = B / 2; st > 0; st /= 2) {
+#pragma unroll
+        for (int i = 0; i < SORT_ITEMS; ++i) {
+            const DsKey c = ((DsKey)kv[i] << 32) | (base + i * SORT_THREADS);
+            bin[i] += c >= s_split_[bin[i] + st] ? st : 0;
+        }
+    }
+    uint32_t pl[SORT_ITEMS];
+#pragma unroll
+    for (int i = 0; i < SORT_ITEMS; ++i)
+        pl[i] = base + i * SORT_THREADS < n ? atomicAdd(&s_cnt[bin[i]], 1u) : 0u;
+    __syncthreads();
+    for (int b = threadIdx.x; b < B; b += SORT_THREADS) {
+        const uint32_t c = s_cnt[b];
+        s_cnt[b] = c ? atomicAdd(&tot[q * s_tot + b], c) : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SORT_ITEMS; ++i) {
+        const uint32_t e = base + i * SORT_THREADS;
+        if (e < n) packed[q * s_keys + e] = (uint32_t)bin[i] << 20 | (s_cnt[bin[i]] + pl[i]);
+    }
+}
+
+// Moves every key (and its index) to its place: bin start + place.
+__global__ __launch_bounds__(SORT_THREADS) void k_depth_move(const uint32_t* __restrict__ keys, size_t s_keys,
+                                                             uint32_t n, int B, const uint32_t* __restrict__ tot,
+                                                             size_t s_tot, const uint32_t* __restrict__ packed,
+                                                             uint32_t* __restrict__ kout, uint32_t* __restrict__ vout)
+{
+    const int q = blockIdx.y;
+    __shared__ uint32_t s_start[DS_MAX_BINS];
+    __shared__ uint32_t wsum[4];
+    const uint32_t base = blockIdx.x * SORT_TILE + threadIdx.x;
+    uint32_t kv[SORT_ITEMS], pv[SORT_ITEMS];
+#pragma unroll
+    for (int i = 0; i < SORT_ITEMS; ++i) {
+        const uint32_t e = base + i * SORT_THREADS;
+        kv[i] = e < n ? keys[q * s_keys + e] : 0u;
+        pv[i] = e < n ? packed[q * s_keys + e] : 0u;
+    }
+    constexpr int BPT = DS_MAX_BINS / SORT_THREADS;
+    uint32_t c[BPT], sum = 0u;
+#pragma unroll
+    for (int k = 0; k < BPT; ++k) {
+        const int b = threadIdx.x * BPT + k;
+        c[k] = b < B ? tot[q * s_tot + b] : 0u;
+        sum += c[k];
+    }
+    uint32_t run = block_exclusive_scan_256(sum, wsum);
+#pragma unroll
+    for (int k = 0; k < BPT; ++k) {
+        s_start[threadIdx.x * BPT + k] = run;
+        run += c[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SORT_ITEMS; ++i) {
+        const uint32_t e = base + i * SORT_THREADS;
+        if (e < n) {
+            const uint32_t dst = s_start[pv[i] >> 20] + (pv[i] & 0xFFFFFu);
+            kout[q * s_keys + dst] = kv[i];
+            vout[q * s_keys + dst] = e;
+        }
+    }
+}
+
+// Sorts one bin (blockIdx.x): kin (keys) and val (indices, in place).
+__global__ __launch_bounds__(64 * DS_WAVES) void k_depth_local(uint32_t* kin, uint32_t* __restrict__ kout,
+                                                               uint32_t* val, size_t s_keys,
+                                                               const uint32_t* __restrict__ tot, size_t s_tot)
+{
+    constexpr int NT = 64 * DS_WAVES;
+    const int q = blockIdx.y, bin = blockIdx.x;
+    __shared__ DsKey x[DS_CAP];
+    const uint32_t m = tot[q * s_tot + bin];
+    if (m == 0) return;
+    uint32_t pre = 0u;
+#pragma unroll
+    for (int k = 0; k < DS_MAX_BINS / 64; ++k) {
+        const int b = k * 64 + (threadIdx.x & 63);
+        pre += b < bin ? tot[q * s_tot + b] : 0u;
+    }
+    for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
+    const size_t base = q * s_keys + (size_t)pre;
+    kin += base;
+    kout += base;
+    val += base;
+    if (m <= NT * 2u) {
+        sort_run<DS_WAVES, 2>(kin, val, kout, val, m, threadIdx.x, x);
+        return;
+    }
+    if (m <= NT * 4u) {
+        sort_run<DS_WAVES, 4>(kin, val, kout, val, m, threadIdx.x, x);
+        return;
+    }
+    if (m <= (uint32_t)DS_CAP) {
+        sort_run<DS_WAVES, 8>(kin, val, kout, val, m, threadIdx.x, x);
+        return;
+    }
+    // the same network on the two arrays in global memory (the missing
+    // elements of the next power of two, infinite, stay where they are)
+    volatile uint32_t* kg = kin;
+    volatile uint32_t* vg = val;
+    uint32_t half = 1u;
+    while (half * 2u < m) half *= 2u;
+    for (uint32_t k = 2; k <= 2u * half; k *= 2u) {
+        for (uint32_t j = k / 2; j > 0; j /= 2u) {
+            for (uint32_t t = threadIdx.x; t < half; t += NT) {
+                const uint32_t r = t & (j - 1u), i = 2u * (t - r) + r, o = i ^ (j == k / 2 ? k - 1u : j);
+                if (o < m) {
+                    const uint32_t ka = kg[i], kb = kg[o], va = vg[i], vb = vg[o];
+                    if (ka > kb || (ka == kb && va > vb)) {
+                        kg[i] = kb;
+                        kg[o] = ka;
+                        vg[i] = vb;
+                        vg[o] = va;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
+    for (uint32_t i = threadIdx.x; i < m; i += NT) kout[i] = kg[i];
+}
+
+size_t depth_keys_in(const Layout& L) { return L.n <= DS_ONE ? L.keys_b : L.keys_a; }
+
+void launch_depth_sort(const Layout& L, char* ws, hipStream_t s)
+{
+    uint32_t *ka = (uint32_t*)(ws + L.keys_a), *kb = (uint32_t*)(ws + L.keys_b);
+    uint32_t *va = (uint32_t*)(ws + L.vals_a), *vb = (uint32_t*)(ws + L.vals_b);
+    const size_t sk = L.s_keys / 4;
+    if (L.n > DS_MAX) {
+        // keys a -> ... -> a after 4 passes (even), values follow
+        radix_sort(ka, kb, va, vb, sk, nullptr, 0, (uint32_t)L.n, 0, 4, L.sort_blocks, L.sort_wide != 0, L, ws, s);
+        return;
+    }
+    const uint32_t n = (uint32_t)L.n;
+    if (L.n <= DS_ONE) {
+        // (the projection left the keys in b)
+        hipLaunchKernelGGL(k_depth_rank<true>, dim3((n + DS_RANK - 1) / DS_RANK, L.nq), dim3(256), 0, s, kb, sk, n,
+                           L.n, (DsKey*)nullptr, (size_t)0, (uint32_t*)nullptr, (size_t)0, ka, va);
+        return;
+    }
+    // (the splitters take 8 bytes per DS_BIN / 2 keys or more: they fit the
+    // count rows, of at least n / 8 bytes)
+    const int B = depth_bins(L.n);
+    DsKey* split = (DsKey*)(ws + L.counts);
+    uint32_t* tot = (uint32_t*)(ws + L.totals);
+    const size_t ss = L.s_counts / sizeof(DsKey), st = L.s_totals / 4;
+    hipLaunchKernelGGL(k_depth_rank<false>, dim3(DS_OVER * B / DS_RANK, L.nq), dim3(256), 0, s, ka, sk, n,
+                       DS_OVER * B, split, ss, tot, st, (uint32_t*)nullptr, (uint32_t*)nullptr);
+    const dim3 grid((n + SORT_TILE - 1) / SORT_TILE, L.nq);
+    hipLaunchKernelGGL(k_depth_bin, grid, dim3(SORT_THREADS), 0, s, ka, sk, n, split, ss, B, tot, st, vb);
+    hipLaunchKernelGGL(k_depth_move, grid, dim3(SORT_THREADS), 0, s, ka, sk, n, B, tot, st, vb, kb, va);
+    hipLaunchKernelGGL(k_depth_local, dim3(B, L.nq), dim3(64 * DS_WAVES), 0, s, kb, ka, va, sk, tot, st);
+}
+
+// ---- tiles-touched scan and pair emission -------------------------------
+// Scan granularity: EMIT_RANKS consecutive depth ranks per workgroup.
+constexpr int EMIT_RANKS = 64;
+// up to this many blocks the emission adds up the block sums itself (each
+// workgroup reads the sums before its own: quadratic, so only for a few
+// thousand blocks)
+constexpr int EMIT_SCAN_BLOCKS = 2048;
 
 // Sum of the tile counts of each EMIT_RANKS block of the depth order (one
 // wave per block).  Culled Gaussians sort to the end (key ~0), so the last
