@@ -677,7 +677,7 @@ template <int NV, bool BIG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_blend_mx(
     BlendJob J, const GRec* __restrict__ rec, const uint32_t* __restrict__ plist, const uint2* __restrict__ ranges,
     const float* __restrict__ attr, float* __restrict__ out, float* __restrict__ T_final,
-    uint32_t* __restrict__ n_last, uint32_t* __restrict__ n_contrib, int min_walk)
+    uint32_t* __restrict__ n_last, uint32_t* __restrict__ n_contrib)
 {
     __shared__ MxWave S[4];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -685,7 +685,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int nb = (J.Fc + 16 * NV - 1) / (16 * NV) * (J.across ? J.nsets : 1);
     const int cb_lo = (int)((int64_t)cg * nb / J.ncg), cb_hi = (int)((int64_t)(cg + 1) * nb / J.ncg);
     blend_mx_unit<NV, BIG>(J, S[wave], tile, wave, set, cb_lo, cb_hi, cg == 0 && set == (J.shared_geo ? 0 : set), rec,
-                           plist, ranges, attr, out, T_final, n_last, n_contrib, min_walk);
+                           plist, ranges, attr, out, T_final, n_last, n_contrib, 0);
+}
+
+// The same over the groups whose walk is longer than min_walk entries, all
+// sets of one geometry: mostly none or a few, so a launch of MX_LONG_GRID
+// workgroups looks for them.  (One workgroup per unit, 3312 of 80 KB of LDS
+// each at 138 tiles and 64 column blocks, waited for LDS beside the training
+// kernels and cost 25 us of a 740 us step to find nothing.)
+constexpr int MX_LONG_GRID = 512;
+
+template <int NV, bool BIG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_blend_mx_long(
+    BlendJob J, const GRec* __restrict__ rec, const uint32_t* __restrict__ plist, const uint2* __restrict__ ranges,
+    const float* __restrict__ attr, float* __restrict__ out, float* __restrict__ T_final,
+    uint32_t* __restrict__ n_last, uint32_t* __restrict__ n_contrib, int items, int min_walk)
+{
+    __shared__ MxWave S[4];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nb = (J.Fc + 16 * NV - 1) / (16 * NV) * J.nsets;
+    for (int it = blockIdx.x; it < items; it += gridDim.x) {
+        const int tile = it / J.ncg, cg = it % J.ncg;
+        const int cb_lo = (int)((int64_t)cg * nb / J.ncg), cb_hi = (int)((int64_t)(cg + 1) * nb / J.ncg);
+        blend_mx_unit<NV, BIG>(J, S[wave], tile, wave, 0, cb_lo, cb_hi, cg == 0, rec, plist, ranges, attr, out,
+                               T_final, n_last, n_contrib, min_walk);
+    }
 }
 
 // Persistent blend over a table of jobs (scenes of any size, grid, tile
@@ -1007,7 +1031,7 @@ void blend_mx_form(BlendJob* J, int64_t n)
                 : 1;
 }
 
-static gs_status launch_mx(BlendJob J, const Layout& L, hipStream_t s, int min_walk)
+static gs_status launch_mx(BlendJob J, const Layout& L, hipStream_t s, int min_walk = 0)
 {
     blend_mx_form(&J, L.n);
     const int nb = (J.Fc + 16 * J.nv - 1) / (16 * J.nv) * (J.across ? J.nsets : 1), z = J.across ? 1 : J.nsets;
@@ -1015,9 +1039,17 @@ static gs_status launch_mx(BlendJob J, const Layout& L, hipStream_t s, int min_w
     if (J.ncg == 0) J.ncg = mx_split((int64_t)L.T * gpt * z, nb, J.nv);
     J.ncg = std::min(J.ncg, nb);
     if ((int64_t)L.T * J.ncg > 0x7FFFFFFF) return GS_ERR_CAPACITY;
+    if (min_walk > 0) {
+        auto kern = J.big ? k_blend_mx_long<1, true>
+                          : (J.nv > 1 ? k_blend_mx_long<MX_WIDE, false> : k_blend_mx_long<1, false>);
+        const int items = L.T * J.ncg;
+        hipLaunchKernelGGL(kern, dim3(std::min(items, MX_LONG_GRID)), dim3(64 * gpt), 0, s, J, J.rec, J.plist,
+                           J.ranges, J.attr, J.out, J.T_final, J.n_last, J.n_contrib, items, min_walk);
+        return GS_OK;
+    }
     auto kern = J.big ? k_blend_mx<1, true> : (J.nv > 1 ? k_blend_mx<MX_WIDE, false> : k_blend_mx<1, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)(L.T * J.ncg), 1, z), dim3(64 * gpt), 0, s, J, J.rec, J.plist, J.ranges,
-                       J.attr, J.out, J.T_final, J.n_last, J.n_contrib, min_walk);
+                       J.attr, J.out, J.T_final, J.n_last, J.n_contrib);
     return GS_OK;
 }
 
@@ -1036,7 +1068,7 @@ gs_status launch_blend(const gs_attrs& a, const gs_params& p, const Layout& L, i
         J.ncg = !J.across && p.chan_group == cg ? Fc / cg : 0;
         void* tok;
         timing_begin(TK_BLEND, s, &tok);
-        const gs_status st = launch_mx(J, L, s, 0);
+        const gs_status st = launch_mx(J, L, s);
         timing_end(tok, s);
         return st;
     }

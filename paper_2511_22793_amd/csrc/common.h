@@ -170,10 +170,6 @@ gs_status lanes_init(int dev);           // creates device dev's lanes (call out
 const Lanes* side_lanes(hipStream_t s);  // the current device's lanes, created unless s is being
                                          // captured; null: the caller runs serially
 std::mutex& lanes_mutex();
-// fills [0, min(per_query * n_dev[q], max_count)) of each query, n_dev read
-// on the device
-void launch_fill_dev(uint32_t* p, size_t max_count, size_t q_stride, int nq, const uint32_t* n_dev, size_t n_stride,
-                     uint32_t per_query, hipStream_t s);
 void launch_project(const gs_scene& sc, const gs_queries& qs, const gs_grid& g, const gs_params& p,
                     const Layout& L, char* ws, hipStream_t s);
 size_t depth_keys_in(const Layout& L);  // where the depth sort reads its keys (offset of the query array)
@@ -222,12 +218,14 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
                            const float* out, const BwdUpstream& up, float* d_attr, hipStream_t s);
 // the shared-geometry compositing / backward over the groups whose walk is
 // longer than min_walk entries only (the long-walk part of the fused
-// training pass); the per-pair geometric accumulators folded per Gaussian
+// training pass); the per-pair geometric accumulators cleared before, and
+// folded per Gaussian after a backward (a forward's walk must be in place)
 void launch_blend_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out,
                           int min_walk, hipStream_t s);
 void launch_blend_bwd_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws,
                               const float* out, const float* target, const float* mean_grad, float scale,
                               const float* gscale, float* d_attr, int min_walk, float* lacc, hipStream_t s);
+void launch_geo_clear(const Layout& L, char* ws, hipStream_t s);
 void launch_geo_fold(const Layout& L, char* ws, hipStream_t s);
 void launch_project_bwd(const gs_scene& sc, const gs_queries& qs, const gs_grid& g, const gs_params& p,
                         const Layout& L, char* ws, float* d_mean, float* d_log_scale, float* d_quat, float* d_opac,

@@ -944,8 +944,7 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
         fs.n = 4;
     }
     launch_fill_segs(fs, s);
-    launch_fill_dev((uint32_t*)(ws + L.gacc), (size_t)L.cap * 8, L.s_gacc / 4, L.nq,
-                    (const uint32_t*)(ws + L.flags) + FL_PUSED, L.s_flags / 4, 8u, s);
+    launch_geo_clear(L, ws, s);
     // hhat, the mean term of g and the channel part of the loss
     hipLaunchKernelGGL(k_train_hsum, dim3(TR_HSUM_BLOCKS, n_sets), dim3(128), 0, s, live_list, live_count,
                        (const float*)(ws + L.wtot), attrs->data, attrs->query_stride, Fc, hs);
@@ -1007,13 +1006,14 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
         if (hipEventRecord(ln->fork, s) != hipSuccess) return GS_ERR_HIP;
         for (int i = 0; i < 3; ++i)
             if (hipStreamWaitEvent(ln->side[i], ln->fork, 0) != hipSuccess) return GS_ERR_HIP;
+        // (first: it mostly finds no group and is gone before the classes fill the CUs)
+        launch_blend_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, TR_EMAX, ln->side[2]);
+        launch_blend_bwd_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, tt->target, mg, escale, tt->grad_scale,
+                                 d_attr, TR_EMAX, llong, ln->side[2]);
         hipLaunchKernelGGL(k_train_fb<TR_EMAX>, dim3(slots.fb[2]), dim3(256), 0, ln->side[0], A, 2);
         hipLaunchKernelGGL(k_train_walk<TR_EMAX>, dim3(slots.walk[2]), dim3(256), 0, ln->side[0], A, 2);
         hipLaunchKernelGGL(k_train_fb<128>, dim3(slots.fb[1]), dim3(256), 0, ln->side[1], A, 1);
         hipLaunchKernelGGL(k_train_walk<128>, dim3(slots.walk[1]), dim3(256), 0, ln->side[1], A, 1);
-        launch_blend_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, TR_EMAX, ln->side[2]);
-        launch_blend_bwd_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, tt->target, mg, escale, tt->grad_scale,
-                                 d_attr, TR_EMAX, llong, ln->side[2]);
         hipLaunchKernelGGL(k_train_fb<64>, dim3(slots.fb[0]), dim3(256), 0, s, A, 0);
         hipLaunchKernelGGL(k_train_walk<64>, dim3(slots.walk[0]), dim3(256), 0, s, A, 0);
         for (int i = 0; i < 3; ++i) {
