@@ -33,10 +33,12 @@
 // differentiated): the running prefix P_k = sum_{m<=k} w_m GV_m, dL/dalpha_k
 // = T_k a_k GV_k - (D - P_k) / (1 - alpha_k) with D = P_last, and the seven
 // geometric terms of each entry reduced over the group's pixels.
+// For walks of at most 128 entries a workgroup takes two neighbouring groups
+// of a tile, four waves each, and sums their dL/dv before the atomics.
 // Both kernels come in variants for walks of at most 64, 128 and 256 list
 // entries (the weights of the whole walk stay in LDS, so the wider variants
-// hold fewer workgroups per CU); a group takes the smallest that holds its
-// walk.  A classification kernel sorts the groups into those three classes
+// hold fewer workgroups per CU); a group, or pair, takes the smallest that
+// holds its walks.  A classification kernel sorts the groups into those three classes
 // (and clears their GV rows); each variant then runs as a persistent grid of
 // the workgroups that fit the chip at once, taking units from its class's
 // list through an atomic counter.  The column split R of a class is chosen
@@ -61,6 +63,11 @@ constexpr int TR_PAD = 68;     // padded LDS row (pixels)
 constexpr int TR_CH = 64;      // entries per alpha chunk
 constexpr int TR_EMAX = 256;   // longest group walk the fused kernels take
 
+// a byte offset past every buffer resource's range: loads there read 0.0f and
+// stores and atomics are dropped, without touching memory (also with a
+// plane's or column's offset added)
+constexpr uint32_t TR_OOB = 0x80000000u;
+
 typedef float f32x4t __attribute__((ext_vector_type(4)));
 
 // pixel k (0 <= k < vw*vh, row-major inside the tile's in-image part) of
@@ -72,36 +79,41 @@ __device__ __forceinline__ int tr_pixel(int k, int vw, int vh, int txi, int tyi,
 
 // The group's pixels, stop positions (the live pass's) and the records of
 // the entries its walk reaches, for walks of at most E entries.
-template <int E>
+// GP: groups of one tile that a workgroup takes together.
+template <int E, int GP = 1>
 struct TrLds {
     double px[E], py[E], ca[E], cb[E], cc[E];
     float sig[E], att[E];
     uint32_t g[E];
-    uint32_t voff[E];      // float offset of the entry's attribute row (g Fc; entry 0's row past the walk)
-    uint32_t nzb[E / 16];  // per block of 16 entries: bit b set if one of them weighs at a pixel of block b
-    int pix[TR_PIX];
-    uint32_t maxstop;
+    alignas(16) uint32_t voff[E];       // byte offset of the entry's attribute row, TR_OOB past the walk
+    alignas(16) uint32_t pofs[GP][TR_PIX];  // byte offset of the pixel in a channel plane, TR_OOB outside
+    unsigned long long nzm[GP];  // bit 4 eb + b: one of the 16 entries of block eb weighs at a pixel of block b
+    int pix[GP][TR_PIX];
+    uint32_t maxstop[GP];
 };
 
-// Shared start of both kernels: returns the walk length m of the group when
-// lo < m <= E (lo = 0: 0 <= m <= E), else -1 (another variant, or the
-// unfused kernels beyond TR_EMAX, takes the group).
-template <int E>
-__device__ __forceinline__ int tr_group(TrLds<E>& L, const GRec* __restrict__ rec,
+// Shared start of both kernels (256 threads per group): `mine` is the walk
+// length of the thread's group; returns the longest of the workgroup's, m, or
+// -1 where it is longer than E (the lists of a class hold none).
+template <int E, int GP>
+__device__ __forceinline__ int tr_group(TrLds<E, GP>& L, const GRec* __restrict__ rec,
                                         const uint32_t* __restrict__ plist, uint2 rg,
-                                        const uint32_t* __restrict__ n_last, int pg, int vw, int vh, int txi, int tyi,
-                                        int tw, int th, int W, int lo, uint32_t& stop)
+                                        const uint32_t* __restrict__ n_last, int pg, bool active, int vw, int vh,
+                                        int txi, int tyi, int tw, int th, int W, uint32_t& stop, int& mine)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) L.maxstop = 0;
-    if (threadIdx.x < TR_PIX) L.pix[threadIdx.x] = tr_pixel(pg * TR_PIX + threadIdx.x, vw, vh, txi, tyi, tw, th, W);
+    const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3, h = GP > 1 ? threadIdx.x >> 8 : 0;
+    const int tid = threadIdx.x & 255;
+    if (threadIdx.x < GP) L.maxstop[threadIdx.x] = 0;
+    if (tid < TR_PIX) L.pix[h][tid] = active ? tr_pixel(pg * TR_PIX + tid, vw, vh, txi, tyi, tw, th, W) : -1;
     __syncthreads();
-    const int mypix = L.pix[lane];
+    const int mypix = L.pix[h][lane];
     stop = mypix >= 0 ? n_last[mypix] : 0u;
-    if (wave == 0 && stop) atomicMax(&L.maxstop, stop);
+    if (wave == 0 && stop) atomicMax(&L.maxstop[h], stop);
     __syncthreads();
-    const uint32_t ms = L.maxstop;
-    if (ms > (uint32_t)E || (lo > 0 && ms <= (uint32_t)lo)) return -1;
+    mine = (int)L.maxstop[h];
+    uint32_t ms = L.maxstop[0];
+    if constexpr (GP > 1) ms = max(ms, L.maxstop[1]);
+    if (ms > (uint32_t)E) return -1;
     const int m = (int)ms;
     for (int t = threadIdx.x; t < m; t += blockDim.x) {
         const uint32_t g = plist[rg.x + t];
@@ -122,12 +134,12 @@ __device__ __forceinline__ int tr_group(TrLds<E>& L, const GRec* __restrict__ re
 // alpha of entries k0 .. k0 + 63 at the lane's pixel, with the walk's
 // decisions applied (0 where the pixel does not take the entry, and beyond
 // the walk), into rows row0 + (k - k0) of s_a; all four waves, no barrier
-template <int E>
-__device__ __forceinline__ void tr_alpha(const TrLds<E>& L, float (*s_a)[TR_PAD], int row0, int k0, int m,
+template <int E, int GP>
+__device__ __forceinline__ void tr_alpha(const TrLds<E, GP>& L, float (*s_a)[TR_PAD], int row0, int k0, int m,
                                          uint32_t stop, int W, float amin, float amax)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int mypix = L.pix[lane];
+    const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
+    const int mypix = L.pix[GP > 1 ? threadIdx.x >> 8 : 0][lane];
     const double pcx = (mypix >= 0 ? mypix % W : 0) + 0.5, pcy = (mypix >= 0 ? mypix / W : 0) + 0.5;
     const double halfW = 0.5 * W;
     for (int kk = wave; kk < TR_CH; kk += TR_WAVES) {
@@ -154,9 +166,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tr_rsrc(const void* base)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7FFFFFFF, 0x00020000);
 }
 
-// One float at byte offset `off` of the buffer; offsets at or past 2^31 - 1
-// (beyond the resource's range) read 0.0f without touching memory.
-constexpr uint32_t TR_OOB = 0x80000000u;
+// One float at byte offset `off` of the buffer.
 __device__ __forceinline__ float tr_ld(__amdgpu_buffer_rsrc_t r, uint32_t off)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
@@ -181,6 +191,7 @@ struct TrArgs {
     float* gv;           // GV accumulators [group][TR_EMAX][TR_PIX] (rows of the walk cleared by the classification)
     double* lacc;        // squared-error sums [S]
     uint32_t* cls;       // group lists of the three walk classes [3][groups]
+    uint32_t* fcls;      // the forward/backward products' lists [3][groups]: first group | member mask << 28
     uint32_t* ctr;       // class sizes, then the work counters of both kernels
     float* gacc;         // per-pair geometric accumulators [pairs][8]
     const float* gscale; // device scale c of every gradient, or null
@@ -189,12 +200,9 @@ struct TrArgs {
     float amin, amax;
 };
 
-// counters: class sizes at TR_CNT + c, units taken by the forward/backward
+// counters: class sizes at TR_CNT + c and TR_FCNT + c, units taken by the forward/backward
 // products at TR_WK_FB + c, groups taken by the backward walk at TR_WK_WALK + c
-constexpr int TR_CNT = 0, TR_WK_FB = 4, TR_WK_WALK = 8, TR_NCTR = 16;
-
-// shortest walk of class c (exclusive; class 0 takes empty walks too)
-__device__ __forceinline__ int tr_lo(int c) { return c == 0 ? 0 : (c == 1 ? 64 : 128); }
+constexpr int TR_CNT = 0, TR_WK_FB = 4, TR_WK_WALK = 8, TR_FCNT = 12, TR_NCTR = 16;
 
 // Column split of a class of `cnt` groups over a persistent grid of `slots`
 // workgroups: enough units to fill the grid, within [rmin, rmax].
@@ -204,25 +212,54 @@ __device__ __forceinline__ int tr_split(const TrArgs& A, uint32_t cnt, int slots
     return min(A.rmax, max(A.rmin, r));
 }
 
-// One wave per group: its walk length (the largest stop position of its
-// pixels), its class, and the GV rows of its walk cleared for the products'
-// atomics.  Groups of no class (walks past TR_EMAX) are left alone.
-__global__ __launch_bounds__(64) void k_train_classify(TrArgs A)
+// One workgroup, a wave per group, for a group or a pair of neighbouring
+// groups of a tile (gp = 1, 2): each group's walk length (the largest stop
+// position of its pixels), its class, and the GV rows of its walk cleared for
+// the products' atomics.  The members of a pair with walks of at most 128
+// entries go to the products together, in the class of the longer; a longer
+// walk goes alone.  Groups of no class (walks past TR_EMAX) are left alone.
+__global__ __launch_bounds__(128) void k_train_classify(TrArgs A, int gp)
 {
-    const int grp = blockIdx.x;
-    const int tile = grp / A.gpt, pg = grp % A.gpt;
-    const int lane = threadIdx.x;
+    const int g0 = blockIdx.x * gp, h = threadIdx.x >> 6;
+    const int grp = g0 + h, tile = grp / A.gpt, pg = grp % A.gpt;
+    const int lane = threadIdx.x & 63;
     const int txi = tile % A.TX, tyi = tile / A.TX;
     const int vw = min(A.tw, A.W - txi * A.tw), vh = min(A.th, A.H - tyi * A.th);
-    if (pg * TR_PIX >= vw * vh) return;
-    const int px = tr_pixel(pg * TR_PIX + lane, vw, vh, txi, tyi, A.tw, A.th, A.W);
-    int m = px >= 0 ? (int)A.n_last[px] : 0;
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    if (m > TR_EMAX) return;
-    const int c = m <= 64 ? 0 : (m <= 128 ? 1 : 2);
-    float4* gv = (float4*)(A.gv + (size_t)grp * TR_EMAX * TR_PIX);
-    for (int i = lane; i < m * (TR_PIX / 4); i += 64) gv[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (lane == 0) A.cls[c * A.groups + atomicAdd(A.ctr + TR_CNT + c, 1u)] = (uint32_t)grp;
+    __shared__ int s_m[2];  // walk lengths; past TR_EMAX: not taken here
+    if (threadIdx.x < 2) s_m[threadIdx.x] = TR_EMAX + 1;
+    __syncthreads();
+    if (pg * TR_PIX < vw * vh) {
+        const int px = tr_pixel(pg * TR_PIX + lane, vw, vh, txi, tyi, A.tw, A.th, A.W);
+        int m = px >= 0 ? (int)A.n_last[px] : 0;
+        for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+        if (lane == 0) s_m[h] = m;
+        if (m <= TR_EMAX) {
+            float4* gv = (float4*)(A.gv + (size_t)grp * TR_EMAX * TR_PIX);
+            for (int i = lane; i < m * (TR_PIX / 4); i += 64) gv[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    uint32_t mask = 0;
+    int mm = 0;
+    for (int k = 0; k < gp; ++k) {
+        const int m = s_m[k];
+        if (m <= 128) {
+            mask |= 1u << k;
+            mm = max(mm, m);
+        } else if (m <= TR_EMAX) {
+            A.cls[2 * A.groups + atomicAdd(A.ctr + TR_CNT + 2, 1u)] = (uint32_t)(g0 + k);
+            A.fcls[2 * A.groups + atomicAdd(A.ctr + TR_FCNT + 2, 1u)] = (uint32_t)(g0 + k) | 1u << 28;
+        }
+    }
+    if (mask == 0) return;
+    // (the walks follow the products of their class on one stream, so both
+    // members are walked in the pair's class)
+    const int c = mm <= 64 ? 0 : 1;
+    A.fcls[c * A.groups + atomicAdd(A.ctr + TR_FCNT + c, 1u)] = (uint32_t)g0 | mask << 28;
+    const uint32_t at = c * A.groups + atomicAdd(A.ctr + TR_CNT + c, (uint32_t)__popc(mask));
+    A.cls[at] = (uint32_t)(g0 + (mask & 1u ? 0 : 1));
+    if (mask == 3u) A.cls[at + 1] = (uint32_t)(g0 + 1);
 }
 
 // occupancy per variant: the LDS of E = 64 fits four workgroups per CU, of
@@ -236,18 +273,34 @@ struct TrOcc {
     static constexpr int sa_rows = E <= 128 ? E : TR_CH;
 };
 
-// One unit (group grp, column range r of R) of kernel 1.  Returns early only
-// for the whole workgroup.
-template <int E>
-__device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (*s_a)[TR_PAD], float (*s_w)[TR_PAD],
-                                           int grp, int r, int R, int lo)
+// the value of the neighbouring lane (lane ^ 1)
+__device__ __forceinline__ float tr_swap1(float v)
 {
-    const int tile = grp / A.gpt, pg = grp % A.gpt;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+
+// One unit (GP groups from g0 on, those in mask; column range r of R) of
+// kernel 1; four waves per group.  Returns early only for the whole workgroup.
+// GP = 2: the groups of a tile walk the same list, so the two sum their
+// attribute gradients (through LDS) before the atomics.  Those run in
+// memory, across the dies, 64 bytes each at a rate that bounded the kernel:
+// 64 sets of 32 complex channels at 180 x 720 took 2.36 ms with one group
+// per workgroup (1.53 with the atomics left out) and 1.97 ms so.
+template <int E, int GP>
+__device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E, GP>& L, float (*sa)[TrOcc<E>::sa_rows][TR_PAD],
+                                           float (*sw)[E][TR_PAD], int g0, uint32_t mask, int r, int R)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int h = GP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+    const int tid = threadIdx.x & 255;
+    float (*s_a)[TR_PAD] = sa[h];
+    float (*s_w)[TR_PAD] = sw[h];
+    const int grp = g0 + h;
+    const bool active = GP == 1 || (mask >> h & 1u);
+    const int tile = g0 / A.gpt, pg = grp % A.gpt;
     const int j4 = lane >> 4, l16 = lane & 15;
     const int txi = tile % A.TX, tyi = tile / A.TX;
     const int vw = min(A.tw, A.W - txi * A.tw), vh = min(A.th, A.H - tyi * A.th);
-    if (pg * TR_PIX >= vw * vh) return;
     const uint2 rg = A.ranges[tile];
     const size_t HW = (size_t)A.H * A.W;
     const int F = A.Fc >> 1;
@@ -257,12 +310,18 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
     // carries c already)
     const float escale = A.gscale ? A.escale * *A.gscale : A.escale;
     uint32_t stop;
-    const int m = tr_group<E>(L, A.rec, A.plist, rg, A.n_last, pg, vw, vh, txi, tyi, A.tw, A.th, A.W, lo, stop);
+    int mine;  // this group's walk; m: the longer of the workgroup's
+    const int m = tr_group<E, GP>(L, A.rec, A.plist, rg, A.n_last, pg, active, vw, vh, txi, tyi, A.tw, A.th, A.W,
+                                  stop, mine);
     if (m < 0) return;
-    const int nks = (m + 3) >> 2;  // K-steps of 4 entries
-    const int mp = nks * 4;
-    const int neb = (m + 15) >> 4;
-    for (int t = threadIdx.x; t < 16 * neb; t += blockDim.x) L.voff[t] = (t < m ? L.g[t] : L.g[0]) * (uint32_t)A.Fc;
+    const int nks = __builtin_amdgcn_readfirstlane((mine + 7) >> 3) * 2;  // K-steps of 4 entries, taken in pairs
+    const int mp = ((m + 7) >> 3) * 8;
+    const int neb = (mine + 15) >> 4;
+    for (int t = threadIdx.x; t < E; t += blockDim.x) L.voff[t] = t < m ? L.g[t] * (uint32_t)A.Fc * 4u : TR_OOB;
+    if (tid < TR_PIX) {
+        const int px = L.pix[h][tid];
+        L.pofs[h][tid] = px >= 0 ? 8u * (uint32_t)px : TR_OOB;
+    }
     __syncthreads();
 
     // The (F) products take the group's pixels in an interleaved order:
@@ -270,7 +329,20 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
     // operands of one K-step (one entry, pixels 4 l16 .. 4 l16 + 3) are one
     // 16-byte LDS read.  A lane then holds rows 4 j4 + i of each block, i.e.
     // pixel 16 j4 + 4 i + pb (read from LDS where used).
-    auto pixY = [&](int pb, int i) -> int { return L.pix[16 * j4 + 4 * i + pb]; };
+    // Target words: a lane's 16 (one column, 16 pixels) are 8 bytes apart, and
+    // lanes of a column pair (re, im of a channel) want alternate words of
+    // the same 128 bytes.  Where the pixels of a pair are neighbours in
+    // memory (an even tile width inside the image) lane c of the column pair
+    // loads 16 bytes, pixels 4 i + 2 c and the next with both words, and the
+    // two exchange halves: 4 loads in 32-byte pieces instead of 16 in single
+    // words, which kept the L1 data path 88% busy.
+    const bool pairs = vw % 2 == 0;
+    const int comp = l16 & 1;
+    const bool full = vw * vh >= (pg + 1) * TR_PIX;  // every pixel of the group is inside the image
+    // The rounds are written without branches around single loads: each
+    // branch made the LDS read or the load before it complete first (one
+    // LDS latency per K-step and per pixel, a third of the kernel).  Steps
+    // past the walk and pixels outside read 0 through TR_OOB.
     const int nrounds = (cb_hi - cb_lo + TR_WAVES - 1) / TR_WAVES;
     // Memory operations complete in issue order for the wait counter, so a
     // wait for a load also waits for every atomic issued before it.  A round
@@ -279,26 +351,52 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
     // wait leaves those atomics in flight.
     constexpr int KCH = (E < 128 ? E : 128) / 4;  // K-steps of one chain
     float bq[KCH];   // V words of the next chain
-    float tcur[16];  // target words of this wave's block
+    float tcur[16];  // target words of this wave's block: pixel 16 j4 + 4 i + pb at 4 i + pb, or as loaded in pairs
+    auto chain_load = [&](__amdgpu_buffer_rsrc_t rv_, int kc_, uint32_t col) {
+        uint32_t vo[KCH];
+#pragma unroll
+        for (int q = 0; q < KCH; ++q) vo[q] = L.voff[4 * (kc_ + q) + j4];
+#pragma unroll
+        for (int q = 0; q < KCH; ++q) bq[q] = tr_ld(rv_, vo[q] + col);
+    };
     auto round_load = [&](int rd_) {
         const int cb_ = cb_lo + rd_ * TR_WAVES + wave;
-        if (rd_ >= nrounds || cb_ >= cb_hi) return;
+        if (rd_ >= nrounds || cb_ >= cb_hi || !active) {
+            // (a wave without a block adds zeros to the others' products)
+#pragma unroll
+            for (int q = 0; q < KCH; ++q) bq[q] = 0.0f;
+            return;
+        }
         const int s_ = cb_ * 16 / A.Fc;
         const int c_ = cb_ * 16 - s_ * A.Fc;
-        const __amdgpu_buffer_rsrc_t rv_ = tr_rsrc(A.attr + s_ * A.a_stride);
-#pragma unroll
-        for (int q = 0; q < KCH; ++q)
-            if (q < nks) bq[q] = tr_ld(rv_, (L.voff[4 * q + j4] + (uint32_t)(c_ + l16)) * 4u);
+        chain_load(tr_rsrc(A.attr + s_ * A.a_stride), 0, (uint32_t)(c_ + l16) * 4u);
         const __amdgpu_buffer_rsrc_t rt = tr_rsrc(A.tgt + (size_t)s_ * F * HW * 2);
         const int cl = c_ + l16;
-        const uint32_t plane = (uint32_t)((cl >> 1) * HW * 2 + (cl & 1));
+        const uint32_t plane = (uint32_t)((cl >> 1) * HW) * 8u;
+        if (pairs) {
+            uint32_t po[4];
 #pragma unroll
-        for (int pb = 0; pb < 4; ++pb)
+            for (int i = 0; i < 4; ++i) po[i] = L.pofs[h][16 * j4 + 4 * i + 2 * comp];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int px = pixY(pb, i);
-                tcur[4 * pb + i] = tr_ld(rt, px >= 0 ? (plane + 2u * px) * 4u : TR_OOB);
+                const float4 t = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rt, plane + po[i], 0, 0));
+                tcur[4 * i] = t.x;
+                tcur[4 * i + 1] = t.y;
+                tcur[4 * i + 2] = t.z;
+                tcur[4 * i + 3] = t.w;
             }
+        } else {
+            uint4 po[4];  // pixels 16 j4 + 4 i + pb
+#pragma unroll
+            for (int i = 0; i < 4; ++i) po[i] = *(const uint4*)&L.pofs[h][16 * j4 + 4 * i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                tcur[4 * i] = tr_ld(rt, plane + 4u * comp + po[i].x);
+                tcur[4 * i + 1] = tr_ld(rt, plane + 4u * comp + po[i].y);
+                tcur[4 * i + 2] = tr_ld(rt, plane + 4u * comp + po[i].z);
+                tcur[4 * i + 3] = tr_ld(rt, plane + 4u * comp + po[i].w);
+            }
+        }
     };
     // the first round's loads fly during the weights' walk
     round_load(0);
@@ -309,8 +407,9 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
     // block) tiles of the weights hold a nonzero value: the products skip
     // the others (their terms are exact zeros)
     float T = 1.0f;
+    unsigned long long nzw = 0ull;
     for (int k0 = 0; k0 < mp; k0 += TR_CH) {
-        tr_alpha<E>(L, s_a, 0, k0, m, stop, A.W, A.amin, A.amax);
+        tr_alpha<E, GP>(L, s_a, 0, k0, m, stop, A.W, A.amin, A.amax);
         __syncthreads();
         if (wave == 0) {
             const int kn = min(TR_CH, mp - k0);
@@ -323,15 +422,24 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
                 nz |= __ballot(w != 0.0f);
                 const int k = k0 + kk;
                 if ((k & 15) == 15 || k == mp - 1) {
-                    if (lane == 0)
-                        L.nzb[k >> 4] = ((nz & 0xFFFFull) ? 1u : 0u) | ((nz & 0xFFFF0000ull) ? 2u : 0u) |
-                                        ((nz & 0xFFFF00000000ull) ? 4u : 0u) | ((nz >> 48) ? 8u : 0u);
+                    nzw |= (unsigned long long)(((nz & 0xFFFFull) ? 1u : 0u) | ((nz & 0xFFFF0000ull) ? 2u : 0u) |
+                                                ((nz & 0xFFFF00000000ull) ? 4u : 0u) | ((nz >> 48) ? 8u : 0u))
+                           << (4 * (k >> 4));
                     nz = 0ull;
                 }
             }
+            if (lane == 0) L.nzm[h] = nzw;
         }
         __syncthreads();
     }
+    auto scalar64 = [](unsigned long long v) -> unsigned long long {
+        return (unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32 |
+               __builtin_amdgcn_readfirstlane((uint32_t)v);
+    };
+    const unsigned long long nzm = scalar64(m > 0 ? L.nzm[h] : 0ull);
+    const unsigned long long nza = GP > 1 ? scalar64(m > 0 ? L.nzm[0] | L.nzm[GP - 1] : 0ull) : nzm;
+    auto weighs = [&](int eb) { return (uint32_t)(nzm >> (4 * eb)) & 15u; };  // pixel blocks of entry block eb
+    auto weighs_any = [&](int eb) { return (uint32_t)(nza >> (4 * eb)) & 15u; };
 
     constexpr int NEB = E / 16;
     f32x4t gv[NEB];  // GV[16 eb + 4 j4 + i][16 wave + l16], over this unit's columns
@@ -342,9 +450,9 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
 
     for (int rd = 0; rd < nrounds; ++rd) {
         const int cb = cb_lo + rd * TR_WAVES + wave;
-        const bool own = cb < cb_hi;
-        const int s = own ? cb * 16 / A.Fc : 0;
-        const int c0 = own ? cb * 16 - s * A.Fc : 0;
+        const bool have = cb < cb_hi, own = have && active;
+        const int s = have ? cb * 16 / A.Fc : 0;
+        const int c0 = have ? cb * 16 - s * A.Fc : 0;
         f32x4t z[4];  // zhat, then g: [pixel 16 j4 + 4 i + pb][column c0 + l16]
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb) z[pb] = f32x4t{0.0f, 0.0f, 0.0f, 0.0f};
@@ -355,21 +463,28 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
             // loaded with the previous round
             const __amdgpu_buffer_rsrc_t rv = tr_rsrc(A.attr + s * A.a_stride);
             for (int kc = 0; kc < nks; kc += KCH) {
-                if (kc > 0) {
+                if (kc > 0) chain_load(rv, kc, (uint32_t)(c0 + l16) * 4u);
+                // the weights of the next pair of steps are read while the
+                // present pair multiplies (the row behind the last is
+                // inside s_w and not used)
+                float4 w0 = *(const float4*)&s_w[4 * kc + j4][4 * l16];
+                float4 w1 = *(const float4*)&s_w[4 * kc + 4 + j4][4 * l16];
 #pragma unroll
-                    for (int q = 0; q < KCH; ++q)
-                        if (kc + q < nks) bq[q] = tr_ld(rv, (L.voff[4 * (kc + q) + j4] + (uint32_t)(c0 + l16)) * 4u);
-                }
-#pragma unroll
-                for (int q = 0; q < KCH; ++q) {
-                    if (kc + q < nks) {
-                        const int ks = kc + q;
-                        const float4 wa = *(const float4*)&s_w[4 * ks + j4][4 * l16];
-                        z[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.x, bq[q], z[0], 0, 0, 0);
-                        z[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.y, bq[q], z[1], 0, 0, 0);
-                        z[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.z, bq[q], z[2], 0, 0, 0);
-                        z[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa.w, bq[q], z[3], 0, 0, 0);
+                for (int q = 0; q < KCH; q += 2) {
+                    if (kc + q >= nks) break;
+                    const float4 a0 = w0, a1 = w1;
+                    if (q + 2 < KCH) {
+                        w0 = *(const float4*)&s_w[4 * (kc + q + 2) + j4][4 * l16];
+                        w1 = *(const float4*)&s_w[4 * (kc + q + 3) + j4][4 * l16];
                     }
+                    z[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, bq[q], z[0], 0, 0, 0);
+                    z[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, bq[q], z[1], 0, 0, 0);
+                    z[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.z, bq[q], z[2], 0, 0, 0);
+                    z[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.w, bq[q], z[3], 0, 0, 0);
+                    z[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, bq[q + 1], z[0], 0, 0, 0);
+                    z[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, bq[q + 1], z[1], 0, 0, 0);
+                    z[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.z, bq[q + 1], z[2], 0, 0, 0);
+                    z[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.w, bq[q + 1], z[3], 0, 0, 0);
                 }
             }
             // target, g, loss partial (column c0 + l16 = channel f, re/im)
@@ -378,26 +493,33 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
             if (A.out) {
                 // the spectrum, on request (one set's spectrum: 32-bit offsets)
                 const __amdgpu_buffer_rsrc_t ro = tr_rsrc(A.out + (size_t)s * F * HW * 2);
-                const uint32_t plane = (uint32_t)((c >> 1) * HW * 2 + (c & 1));
+                const uint32_t plane = (uint32_t)((c >> 1) * HW * 2 + (c & 1)) * 4u;
 #pragma unroll
                 for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int px = pixY(pb, i);
-                        const float zv = z[pb][i];
-                        if (px >= 0)
-                            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(zv), ro, (plane + 2u * px) * 4u, 0,
-                                                                  0);
-                    }
+                    for (int i = 0; i < 4; ++i)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(z[pb][i]), ro,
+                                                              plane + L.pofs[h][16 * j4 + 4 * i + pb], 0, 0);
+            }
+            if (pairs) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float a0 = tcur[4 * i], a1 = tcur[4 * i + 1], b0 = tcur[4 * i + 2], b1 = tcur[4 * i + 3];
+                    const float m0 = comp ? a1 : a0, m1 = comp ? b1 : b0;
+                    const float r0 = tr_swap1(comp ? a0 : a1), r1 = tr_swap1(comp ? b0 : b1);
+                    tcur[4 * i] = comp ? r0 : m0;
+                    tcur[4 * i + 1] = comp ? r1 : m1;
+                    tcur[4 * i + 2] = comp ? m0 : r0;
+                    tcur[4 * i + 3] = comp ? m1 : r1;
+                }
             }
             float ls = 0.0f;
 #pragma unroll
             for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int px = pixY(pb, i);
-                    if (px >= 0) {
-                        const float d = z[pb][i] - tcur[4 * pb + i];
+                    const float d = z[pb][i] - tcur[4 * i + pb];
+                    if (full || L.pix[h][16 * j4 + 4 * i + pb] >= 0) {
                         ls = fmaf(d, d, ls);
                         z[pb][i] = fmaf(escale, d, mc);
                     } else {
@@ -413,20 +535,17 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
                 lsum = 0.0f;
             }
             lsum += ls;
-            // g to LDS for (G): s_a[16 wave + j][p] = g(p, c0 + j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float g0 = z[0][i], g1 = z[1][i], g2 = z[2][i], g3 = z[3][i];
-                *(float4*)&s_a[16 * wave + l16][16 * j4 + 4 * i] = float4{g0, g1, g2, g3};
-            }
         }
+        // g to LDS for (G): s_a[16 wave + j][p] = g(p, c0 + j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *(float4*)&s_a[16 * wave + l16][16 * j4 + 4 * i] = float4{z[0][i], z[1][i], z[2][i], z[3][i]};
         __syncthreads();
         // (G) GV[k][16 wave + l16] += sum over the round's columns of v(k, c) g(p, c)
         if constexpr (E <= 128) {
             // The round's V block is the four waves' (F) operands: it goes
             // through s_a too (after each wave has taken its g words), so
             // that no wave reads the other waves' columns from memory.
-            const int nown = min(TR_WAVES, cb_hi - (cb_lo + rd * TR_WAVES));
             float bg[TR_WAVES][4];
 #pragma unroll
             for (int ow = 0; ow < TR_WAVES; ++ow)
@@ -434,24 +553,25 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
                 for (int kk = 0; kk < 4; ++kk) bg[ow][kk] = s_a[16 * ow + 4 * j4 + kk][16 * wave + l16];
             __syncthreads();
             // s_a[k][16 ow + j] = v(k, column j of owner ow's block)
-            if (own) {
 #pragma unroll
-                for (int q = 0; q < KCH; ++q)
-                    if (q < nks) s_a[4 * q + j4][16 * wave + l16] = bq[q];
-            }
+            for (int q = 0; q < KCH; q += 4)
+                if (q < nks) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) s_a[4 * (q + u) + j4][16 * wave + l16] = bq[q + u];
+                }
             __syncthreads();
 #pragma unroll
             for (int eb = 0; eb < NEB; ++eb) {
-                if (eb < neb && (__builtin_amdgcn_readfirstlane(L.nzb[eb]) & (1u << wave))) {
+                if (weighs(eb) & (1u << wave)) {
+                    float4 v4[TR_WAVES];
+#pragma unroll
+                    for (int ow = 0; ow < TR_WAVES; ++ow) v4[ow] = *(const float4*)&s_a[16 * eb + l16][16 * ow + 4 * j4];
 #pragma unroll
                     for (int ow = 0; ow < TR_WAVES; ++ow) {
-                        if (ow < nown) {
-                            const float4 v4 = *(const float4*)&s_a[16 * eb + l16][16 * ow + 4 * j4];
-                            gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4.x, bg[ow][0], gv[eb], 0, 0, 0);
-                            gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4.y, bg[ow][1], gv[eb], 0, 0, 0);
-                            gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4.z, bg[ow][2], gv[eb], 0, 0, 0);
-                            gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4.w, bg[ow][3], gv[eb], 0, 0, 0);
-                        }
+                        gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4[ow].x, bg[ow][0], gv[eb], 0, 0, 0);
+                        gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4[ow].y, bg[ow][1], gv[eb], 0, 0, 0);
+                        gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4[ow].z, bg[ow][2], gv[eb], 0, 0, 0);
+                        gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4[ow].w, bg[ow][3], gv[eb], 0, 0, 0);
                     }
                 }
             }
@@ -468,10 +588,10 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
             for (int kk = 0; kk < 4; ++kk) bg[kk] = s_a[16 * ow + 4 * j4 + kk][16 * wave + l16];
 #pragma unroll
             for (int eb = 0; eb < NEB; ++eb) {
-                if (eb < neb && (__builtin_amdgcn_readfirstlane(L.nzb[eb]) & (1u << wave))) {
+                if (weighs(eb) & (1u << wave)) {
                     const float4 v4 = __builtin_bit_cast(
                         float4, __builtin_amdgcn_raw_buffer_load_b128(
-                                    rv, (L.voff[16 * eb + l16] + (uint32_t)(oc0 + 4 * j4)) * 4u, 0, 0));
+                                    rv, L.voff[16 * eb + l16] + (uint32_t)(oc0 + 4 * j4) * 4u, 0, 0));
                     __builtin_amdgcn_sched_barrier(0);
                     gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4.x, bg[0], gv[eb], 0, 0, 0);
                     gv[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4.y, bg[1], gv[eb], 0, 0, 0);
@@ -488,29 +608,54 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
 #pragma unroll
         for (int eb = 0; eb < NEB; ++eb) {
             acc[eb] = f32x4t{0.0f, 0.0f, 0.0f, 0.0f};
-            if (own && eb < neb && __builtin_amdgcn_readfirstlane(L.nzb[eb])) {
+            if (own && weighs(eb)) {
+                float4 w4[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w4[i] = *(const float4*)&s_w[16 * eb + l16][16 * j4 + 4 * i];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float4 w4 = *(const float4*)&s_w[16 * eb + l16][16 * j4 + 4 * i];
-                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4.x, z[0][i], acc[eb], 0, 0, 0);
-                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4.y, z[1][i], acc[eb], 0, 0, 0);
-                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4.z, z[2][i], acc[eb], 0, 0, 0);
-                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4.w, z[3][i], acc[eb], 0, 0, 0);
+                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i].x, z[0][i], acc[eb], 0, 0, 0);
+                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i].y, z[1][i], acc[eb], 0, 0, 0);
+                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i].z, z[2][i], acc[eb], 0, 0, 0);
+                    acc[eb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i].w, z[3][i], acc[eb], 0, 0, 0);
                 }
             }
         }
         round_load(rd + 1);
-        if (own) {
+        if constexpr (GP > 1) {
+            // the groups' sums: each takes every other entry block
+            float* mine_x = &s_a[0][0] + wave * (NEB / 2 * 256);
+            const float* other_x = &sa[1 - h][0][0] + wave * (NEB / 2 * 256);
+            __syncthreads();  // s_a is read
+#pragma unroll
+            for (int b = 0; b < NEB / 2; ++b) {
+                const f32x4t o = h ? acc[2 * b] : acc[2 * b + 1];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mine_x[(4 * b + i) * 64 + lane] = o[i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int b = 0; b < NEB / 2; ++b) {
+                f32x4t t = h ? acc[2 * b + 1] : acc[2 * b];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t[i] += other_x[(4 * b + i) * 64 + lane];
+                acc[b] = t;  // block 2 b + h
+            }
+        }
+        if (have) {
             const __amdgpu_buffer_rsrc_t rd_attr = tr_rsrc(A.d_attr + s * A.da_stride);
+            const uint32_t col = (uint32_t)(c0 + l16) * 4u;
 #pragma unroll
-            for (int eb = 0; eb < NEB; ++eb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = 16 * eb + 4 * j4 + i;
-                    if (k < m && acc[eb][i] != 0.0f)
-                        __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(
-                            acc[eb][i], rd_attr, (L.voff[k] + (uint32_t)(c0 + l16)) * 4u, 0, 0);
+            for (int b = 0; b < NEB / GP; ++b) {
+                const int eb = GP * b + h;
+                if (weighs_any(eb)) {
+                    const uint4 vo = *(const uint4*)&L.voff[16 * eb + 4 * j4];
+                    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(acc[b][0], rd_attr, vo.x + col, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(acc[b][1], rd_attr, vo.y + col, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(acc[b][2], rd_attr, vo.z + col, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(acc[b][3], rd_attr, vo.w + col, 0, 0);
                 }
+            }
         }
         __syncthreads();  // before the next round's g overwrites s_a
     }
@@ -530,23 +675,23 @@ __device__ __forceinline__ void tr_fb_unit(const TrArgs& A, TrLds<E>& L, float (
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int k = 16 * eb + 4 * j4 + i;
-                if (k < m && gv[eb][i] != 0.0f)
+                if (k < mine && gv[eb][i] != 0.0f)
                     __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(gv[eb][i], rg_gv, lane_off + i * TR_PIX * 4,
                                                                     eb * 16 * TR_PIX * 4, 0);
             }
 }
 
 // Kernel 1 as a persistent grid over the units of walk class c.
-template <int E>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TrOcc<E>::waves))) void k_train_fb(TrArgs A,
-                                                                                                      int c)
+template <int E, int GP>
+__global__ __launch_bounds__(256 * GP) __attribute__((amdgpu_waves_per_eu(TrOcc<E>::waves))) void k_train_fb(TrArgs A,
+                                                                                                           int c)
 {
-    __shared__ TrLds<E> L;
+    __shared__ TrLds<E, GP> L;
     // alpha of a chunk, then the exchange of g, then (E <= 128) the round's V block
-    __shared__ __align__(16) float s_a[TrOcc<E>::sa_rows][TR_PAD];
-    __shared__ __align__(16) float s_w[E][TR_PAD];      // weights w_k(p)
+    __shared__ __align__(16) float s_a[GP][TrOcc<E>::sa_rows][TR_PAD];
+    __shared__ __align__(16) float s_w[GP][E][TR_PAD];  // weights w_k(p)
     __shared__ uint32_t s_item;
-    const uint32_t cnt = A.ctr[TR_CNT + c];
+    const uint32_t cnt = A.ctr[TR_FCNT + c];
     const int R = tr_split(A, cnt, (int)gridDim.x);
     const uint32_t total = cnt * (uint32_t)R;
     for (;;) {
@@ -555,7 +700,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TrOcc<E>::w
         const uint32_t item = s_item;
         __syncthreads();
         if (item >= total) break;
-        tr_fb_unit<E>(A, L, s_a, s_w, (int)A.cls[c * A.groups + item / R], (int)(item % R), R, tr_lo(c));
+        const uint32_t f = A.fcls[c * A.groups + item / R];
+        tr_fb_unit<E, GP>(A, L, s_a, s_w, (int)(f & 0x0FFFFFFFu), f >> 28, (int)(item % R), R);
         __syncthreads();  // the next unit reuses the LDS
     }
 }
@@ -603,7 +749,7 @@ __device__ __forceinline__ void tr_reduce_scatter8(float* x, int lane)
 
 template <int E>
 __device__ __forceinline__ void tr_walk_group(const TrArgs& A, TrLds<E>& L, float (*s_a)[TR_PAD],
-                                              float (*s_gv)[TR_PAD], int grp, int lo)
+                                              float (*s_gv)[TR_PAD], int grp)
 {
     const int tile = grp / A.gpt, pg = grp % A.gpt;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -612,9 +758,10 @@ __device__ __forceinline__ void tr_walk_group(const TrArgs& A, TrLds<E>& L, floa
     if (pg * TR_PIX >= vw * vh) return;
     const uint2 rg = A.ranges[tile];
     uint32_t stop;
-    const int m = tr_group<E>(L, A.rec, A.plist, rg, A.n_last, pg, vw, vh, txi, tyi, A.tw, A.th, A.W, lo, stop);
+    int mine;
+    const int m = tr_group<E, 1>(L, A.rec, A.plist, rg, A.n_last, pg, true, vw, vh, txi, tyi, A.tw, A.th, A.W, stop, mine);
     if (m <= 0) return;
-    for (int k0 = 0; k0 < m; k0 += TR_CH) tr_alpha<E>(L, s_a, k0, k0, m, stop, A.W, A.amin, A.amax);
+    for (int k0 = 0; k0 < m; k0 += TR_CH) tr_alpha<E, 1>(L, s_a, k0, k0, m, stop, A.W, A.amin, A.amax);
     const float4* gp = (const float4*)(A.gv + (size_t)grp * TR_EMAX * TR_PIX);
     for (int e = threadIdx.x; e < m * (TR_PIX / 4); e += blockDim.x)
         *(float4*)&s_gv[e / (TR_PIX / 4)][4 * (e % (TR_PIX / 4))] = gp[e];
@@ -648,7 +795,7 @@ __device__ __forceinline__ void tr_walk_group(const TrArgs& A, TrLds<E>& L, floa
     }
     __syncthreads();
     // geometric terms of entry k at this lane's pixel, reduced over the pixels
-    const int mypix = L.pix[lane];
+    const int mypix = L.pix[0][lane];
     const double pcx = (mypix >= 0 ? mypix % A.W : 0) + 0.5, pcy = (mypix >= 0 ? mypix / A.W : 0) + 0.5;
     const double halfW = 0.5 * A.W;
     for (int k = wave; k < m; k += TR_WAVES) {
@@ -694,7 +841,7 @@ __global__ __launch_bounds__(256) void k_train_walk(TrArgs A, int c)
         const uint32_t item = s_item;
         __syncthreads();
         if (item >= cnt) break;
-        tr_walk_group<E>(A, L, s_a, s_gv, (int)A.cls[c * A.groups + item], tr_lo(c));
+        tr_walk_group<E>(A, L, s_a, s_gv, (int)A.cls[c * A.groups + item]);
         __syncthreads();  // the next group reuses the LDS
     }
 }
@@ -813,7 +960,7 @@ __global__ __launch_bounds__(256) void k_spatial_mean(const float* __restrict__ 
 
 // Scratch layout of gs_render_train (byte offsets from its start).
 struct TrScratch {
-    size_t gv, lacc, llong, hs, mg, cls, ctr, total;
+    size_t gv, lacc, llong, hs, mg, cls, fcls, ctr, total;
 };
 TrScratch train_scratch(int groups, int S, int Fc)
 {
@@ -824,7 +971,8 @@ TrScratch train_scratch(int groups, int S, int Fc)
     t.hs = t.llong + align256((size_t)S * 4);
     t.mg = t.hs + align256((size_t)S * Fc * 4);
     t.cls = t.mg + align256((size_t)S * Fc * 4);
-    t.ctr = t.cls + align256((size_t)3 * groups * 4);
+    t.fcls = t.cls + align256((size_t)3 * groups * 4);
+    t.ctr = t.fcls + align256((size_t)3 * groups * 4);
     t.total = t.ctr + align256((size_t)TR_NCTR * 4);
     return t;
 }
@@ -832,7 +980,7 @@ TrScratch train_scratch(int groups, int S, int Fc)
 // Workgroups of each variant resident on the whole device at once (the
 // persistent grids), per device.
 struct TrSlots {
-    int fb[3], walk[3];
+    int fb[3], fb2[2], walk[3];  // fb2: two groups per workgroup
 };
 hipError_t train_slots(TrSlots* out)
 {
@@ -847,7 +995,9 @@ hipError_t train_slots(TrSlots* out)
     if (!have[dev]) {
         int cus = 0;
         if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        const void* fb[3] = {(const void*)k_train_fb<64>, (const void*)k_train_fb<128>, (const void*)k_train_fb<256>};
+        const void* fb[3] = {(const void*)k_train_fb<64, 1>, (const void*)k_train_fb<128, 1>,
+                             (const void*)k_train_fb<256, 1>};
+        const void* fb2[2] = {(const void*)k_train_fb<64, 2>, (const void*)k_train_fb<128, 2>};
         const void* wk[3] = {(const void*)k_train_walk<64>, (const void*)k_train_walk<128>,
                              (const void*)k_train_walk<256>};
         for (int c = 0; c < 3; ++c) {
@@ -856,6 +1006,11 @@ hipError_t train_slots(TrSlots* out)
             if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, wk[c], 256, 0)) != hipSuccess) return e;
             cache[dev].fb[c] = std::max(1, a) * std::max(1, cus);
             cache[dev].walk[c] = std::max(1, b) * std::max(1, cus);
+        }
+        for (int c = 0; c < 2; ++c) {
+            int a = 0;
+            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, fb2[c], 512, 0)) != hipSuccess) return e;
+            cache[dev].fb2[c] = std::max(1, a) * std::max(1, cus);
         }
         have[dev] = 1;
     }
@@ -967,6 +1122,7 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
     A.gv = (float*)(sc + ts.gv);
     A.lacc = lacc;
     A.cls = (uint32_t*)(sc + ts.cls);
+    A.fcls = (uint32_t*)(sc + ts.fcls);
     A.ctr = ctr;
     A.gacc = (float*)(ws + L.gacc);
     A.gscale = tt->grad_scale;
@@ -990,7 +1146,21 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
     timing_begin(TK_TRAIN, s, &tok);
     // the groups sorted by walk length into the variants' lists, then each
     // variant over its list (the longest walks first)
-    hipLaunchKernelGGL(k_train_classify, dim3(groups), dim3(64), 0, s, A);
+    // (tiles of 64 pixels have one group: no pairs)
+    const int gp = gpt > 1 ? 2 : 1;
+    auto products = [&](int c, hipStream_t st_) {
+        if (c == 2)
+            hipLaunchKernelGGL((k_train_fb<TR_EMAX, 1>), dim3(slots.fb[2]), dim3(256), 0, st_, A, 2);
+        else if (gp == 2 && c == 1)
+            hipLaunchKernelGGL((k_train_fb<128, 2>), dim3(slots.fb2[1]), dim3(512), 0, st_, A, 1);
+        else if (gp == 2)
+            hipLaunchKernelGGL((k_train_fb<64, 2>), dim3(slots.fb2[0]), dim3(512), 0, st_, A, 0);
+        else if (c == 1)
+            hipLaunchKernelGGL((k_train_fb<128, 1>), dim3(slots.fb[1]), dim3(256), 0, st_, A, 1);
+        else
+            hipLaunchKernelGGL((k_train_fb<64, 1>), dim3(slots.fb[0]), dim3(256), 0, st_, A, 0);
+    };
+    hipLaunchKernelGGL(k_train_classify, dim3(groups / gp), dim3(64 * gp), 0, s, A, gp);
     // The classes touch disjoint groups (their GV rows, work counters and
     // lists; the attribute gradients, loss partials and per-pair sums are
     // atomics), so the 256 and 128 classes run on side streams beside the
@@ -1010,11 +1180,11 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
         launch_blend_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, TR_EMAX, ln->side[2]);
         launch_blend_bwd_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, tt->target, mg, escale, tt->grad_scale,
                                  d_attr, TR_EMAX, llong, ln->side[2]);
-        hipLaunchKernelGGL(k_train_fb<TR_EMAX>, dim3(slots.fb[2]), dim3(256), 0, ln->side[0], A, 2);
+        products(2, ln->side[0]);
         hipLaunchKernelGGL(k_train_walk<TR_EMAX>, dim3(slots.walk[2]), dim3(256), 0, ln->side[0], A, 2);
-        hipLaunchKernelGGL(k_train_fb<128>, dim3(slots.fb[1]), dim3(256), 0, ln->side[1], A, 1);
+        products(1, ln->side[1]);
         hipLaunchKernelGGL(k_train_walk<128>, dim3(slots.walk[1]), dim3(256), 0, ln->side[1], A, 1);
-        hipLaunchKernelGGL(k_train_fb<64>, dim3(slots.fb[0]), dim3(256), 0, s, A, 0);
+        products(0, s);
         hipLaunchKernelGGL(k_train_walk<64>, dim3(slots.walk[0]), dim3(256), 0, s, A, 0);
         for (int i = 0; i < 3; ++i) {
             if (hipEventRecord(ln->join[i], ln->side[i]) != hipSuccess) return GS_ERR_HIP;
@@ -1022,9 +1192,9 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
         }
         timing_end(tok, s);
     } else {
-        hipLaunchKernelGGL(k_train_fb<TR_EMAX>, dim3(slots.fb[2]), dim3(256), 0, s, A, 2);
-        hipLaunchKernelGGL(k_train_fb<128>, dim3(slots.fb[1]), dim3(256), 0, s, A, 1);
-        hipLaunchKernelGGL(k_train_fb<64>, dim3(slots.fb[0]), dim3(256), 0, s, A, 0);
+        products(2, s);
+        products(1, s);
+        products(0, s);
         hipLaunchKernelGGL(k_train_walk<TR_EMAX>, dim3(slots.walk[2]), dim3(256), 0, s, A, 2);
         hipLaunchKernelGGL(k_train_walk<128>, dim3(slots.walk[1]), dim3(256), 0, s, A, 1);
         hipLaunchKernelGGL(k_train_walk<64>, dim3(slots.walk[0]), dim3(256), 0, s, A, 0);
