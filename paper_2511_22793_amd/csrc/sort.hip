@@ -766,27 +766,51 @@ __global__ __launch_bounds__(64) void k_scan_reduce(const uint32_t* __restrict__
 }
 
 // Exclusive scan of the block sums; records the pair count and overflow.
-__global__ __launch_bounds__(256) void k_scan_top(uint32_t* __restrict__ partial, size_t s_partial, int nblocks,
-                                                  uint32_t* __restrict__ flags, size_t s_flags, int64_t cap)
+// One workgroup, latency-bound: 8 sums per thread in one pass up to 524,288
+// Gaussians (4688 sums: 15 us by 256 threads, one sum each at a time, ST_NOW so).
+__global__ __launch_bounds__(1024) void k_scan_top(uint32_t* __restrict__ partial, size_t s_partial, int nblocks,
+                                                   uint32_t* __restrict__ flags, size_t s_flags, int64_t cap)
 {
-    const int q = blockIdx.x;
+    constexpr int IT = 8;
+    const int q = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
     partial += q * s_partial;
     flags += q * s_flags;
-    __shared__ uint32_t wsum[4];
-    __shared__ unsigned long long carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int b0 = 0; b0 < nblocks; b0 += 256) {
-        const int b = b0 + threadIdx.x;
-        const uint32_t v = b < nblocks ? partial[b] : 0u;
-        const uint32_t ex = block_exclusive_scan_256(v, wsum);
-        const unsigned long long c = carry;
-        if (b < nblocks) partial[b] = (uint32_t)(c + ex);
+    __shared__ unsigned long long wsum[16];
+    unsigned long long carry = 0;
+    for (int b0 = 0; b0 < nblocks; b0 += 1024 * IT) {
+        uint32_t v[IT];
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int b = b0 + t * IT + i;
+            v[i] = b < nblocks ? partial[b] : 0u;
+        }
+        unsigned long long sum = 0;
+#pragma unroll
+        for (int i = 0; i < IT; ++i) sum += v[i];
+        unsigned long long x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wsum[w] = x;
         __syncthreads();
-        if (threadIdx.x == 255) carry = c + ex + v;
-        __syncthreads();
+        unsigned long long run = carry + x - sum;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const unsigned long long ws = wsum[k];
+            run += k < w ? ws : 0ull;
+            carry += ws;
+        }
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int b = b0 + t * IT + i;
+            if (b < nblocks) partial[b] = (uint32_t)run;
+            run += v[i];
+        }
+        __syncthreads();  // the next chunk's sums
     }
-    if (threadIdx.x == 0) {
+    if (t == 0) {
         const unsigned long long P = carry;
         flags[FL_PAIRS] = (uint32_t)(P > 0xFFFFFFFFull ? 0xFFFFFFFFull : P);
         flags[FL_OVERFLOW] = P > (unsigned long long)cap ? 1u : 0u;
@@ -922,7 +946,7 @@ void launch_binning(const Layout& L, char* ws, hipStream_t s)
         hipLaunchKernelGGL(k_emit<true>, dim3(nblk, L.nq), dim3(256), 0, s, order, so, tinfo, sti, flags, sf,
                            partial, sp, pa, spk, L.cap, L.TX, L.rank_bits);
     } else {
-        hipLaunchKernelGGL(k_scan_top, dim3(L.nq), dim3(256), 0, s, partial, sp, nblk, flags, sf, L.cap);
+        hipLaunchKernelGGL(k_scan_top, dim3(L.nq), dim3(1024), 0, s, partial, sp, nblk, flags, sf, L.cap);
         hipLaunchKernelGGL(k_emit<false>, dim3(nblk, L.nq), dim3(256), 0, s, order, so, tinfo, sti, flags, sf,
                            partial, sp, pa, spk, L.cap, L.TX, L.rank_bits);
     }
