@@ -767,7 +767,7 @@ __global__ __launch_bounds__(64) void k_scan_reduce(const uint32_t* __restrict__
 
 // Exclusive scan of the block sums; records the pair count and overflow.
 // One workgroup, latency-bound: 8 sums per thread in one pass up to 524,288
-// Gaussians (4688 sums: 15 us by 256 threads, one sum each at a time, ST_NOW so).
+// Gaussians (4688 sums: 15 us by 256 threads, one sum each at a time, 6 so).
 __global__ __launch_bounds__(1024) void k_scan_top(uint32_t* __restrict__ partial, size_t s_partial, int nblocks,
                                                    uint32_t* __restrict__ flags, size_t s_flags, int64_t cap)
 {

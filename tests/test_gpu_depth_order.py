@@ -56,3 +56,7 @@ def test_depth_order_exact(n, kind):
         assert np.array_equal(got, np.concatenate([order, culled]))
         assert np.array_equal(keys[:len(order)], p["r32"][order].view(np.uint32))
         assert np.all(keys[len(order):] == 0xFFFFFFFF)
+        # the scan of the tile counts behind it (8193 block sums at the largest)
+        tiles = ws.view("tinfo", q, 4 * n, torch.int32).cpu().numpy().reshape(n, 4)[:, 3]
+        f = ws.flags()[q]
+        assert f["n_visible"] == len(order) and f["n_pairs"] == int(tiles[order].astype(np.int64).sum())
