@@ -7,8 +7,8 @@
 // Parameters are stored per parameter index, then per Gaussian
 // (params[k * stride + i], k < 6H + 2: W1 [H][3], b1 [H], W2 [2][H], b2 [2]),
 // so that one load instruction of a wave reads 64 consecutive Gaussians.
-// One thread per Gaussian (H = 8, 16; eight lanes per Gaussian at H = 64)
-// holds its parameters in registers and takes every query, so the parameters
+// One thread per Gaussian (H = 8, and 16 forward; two lanes per Gaussian for
+// the width-16 backward, eight at H = 64) holds its parameters in registers and takes every query, so the parameters
 // leave HBM once per launch (a batched matrix-vector product: HBM-bound, not
 // a matrix-core shape).
 #include "common.h"
@@ -251,8 +251,16 @@ __global__ __launch_bounds__(256) void k_emission_bwd_split(const float* __restr
     const float b20 = em_ld(rp, off.b2, 0), b21 = em_ld(rp, off.b2, rs);
     const float m0 = mean[ii], m1 = mean[n + ii], m2 = mean[2 * n + ii];
     float gb20 = 0.0f, gb21 = 0.0f, gm0 = 0.0f, gm1 = 0.0f, gm2 = 0.0f;
+    // the upstream words of the next two queries are on their way meanwhile
+    auto up_at = [&](int q) -> float2 {
+        return q < nq ? ((const float2*)(dattr + q * as))[ii] : float2{0.0f, 0.0f};
+    };
+    float2 up1 = up_at(0), up2 = up_at(1);
 #pragma unroll 1
     for (int q = 0; q < nq; ++q) {
+        const float2 up = up1;
+        up1 = up2;
+        up2 = up_at(q + 2);
         const float x0 = rx[3 * q], x1 = rx[3 * q + 1], x2 = rx[3 * q + 2];
         float z[HS];
         float f0 = 0.0f, f1 = 0.0f;
@@ -270,7 +278,6 @@ __global__ __launch_bounds__(256) void k_emission_bwd_split(const float* __restr
         const float d = fmaxf(dist, r_near);
         const float ld = logf(d);
         const float s0 = em_sigmoid(f0 - ld), s1 = em_sigmoid(f1 - ld);
-        const float2 up = ((const float2*)(dattr + q * as))[ii];
         const float u0 = up.x * s0 * (1.0f - s0), u1 = up.y * s1 * (1.0f - s1);
         gb20 += u0;
         gb21 += u1;
@@ -314,6 +321,12 @@ __global__ __launch_bounds__(256) void k_emission_bwd_split(const float* __restr
 
 // lanes per Gaussian of the width-64 kernels
 constexpr int EM_SPLIT = 8;
+// and of the width-16 backward: its 98 parameters and 98 gradients alone take
+// a lane's 256 registers, one wave per SIMD, and 100,000 Gaussians are 1.5 waves
+// per SIMD, two rounds.  Two lanes take 8 hidden units each at three waves
+// per SIMD (16 queries: 49 us with one lane, 36 us so).  Rows past the 32-bit
+// byte offsets of the split form keep the one-lane kernel.
+constexpr int EM_SPLIT16 = 2;
 
 static gs_status em_check(const float* P, int64_t ps, const float* mean, int n, const float* rx, const float* tx,
                           int nq, float r_near, int64_t as)
@@ -364,6 +377,11 @@ extern "C" gs_status gs_emission_backward(const float* params, int64_t param_str
     if (hidden == 64) {
         constexpr int per_block = 256 / EM_SPLIT;
         hipLaunchKernelGGL((k_emission_bwd_split<64, EM_SPLIT>), dim3((n + per_block - 1) / per_block), dim3(256), 0,
+                           (hipStream_t)stream, params, param_stride, mean, n, rx, tx, n_queries, r_near, d_attr,
+                           attr_query_stride, d_params, d_mean);
+    } else if (hidden == 16 && (uint64_t)em_np(16) * (uint64_t)param_stride * 4 < (1ull << 31)) {
+        constexpr int per_block = 256 / EM_SPLIT16;
+        hipLaunchKernelGGL((k_emission_bwd_split<16, EM_SPLIT16>), dim3((n + per_block - 1) / per_block), dim3(256), 0,
                            (hipStream_t)stream, params, param_stride, mean, n, rx, tx, n_queries, r_near, d_attr,
                            attr_query_stride, d_params, d_mean);
     } else {

@@ -104,3 +104,23 @@ def test_emission_feeds_the_renderer():
     ref_attr = er.forward(P, sc["mean"].T, rx, tx)[0].reshape(n, 1, 2)
     ref = oracle.render(sc, ref_attr, rx[0], 90, 360)
     check_parity(got[0], ref, "emission -> render")
+
+
+@pytest.mark.parametrize("n", [1, 31, 127, 300])
+def test_backward_of_both_lane_splits_agree(n):
+    """Width 16: two lanes per Gaussian, and one lane where the parameter rows
+    pass the 32-bit byte offsets (the same network in rows 5.5 million floats
+    apart).  The two order the 16 hidden units' sums differently: a few FP32
+    roundings, 1e-5 of each tensor's maximum."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    P = torch.randn(98, n, device="cuda", generator=g) * 0.3
+    mean = torch.randn(3, n, device="cuda", generator=g)
+    rx, tx = (torch.randn(5, 3, device="cuda", generator=g) for _ in range(2))
+    up = torch.randn(5, n, 2, device="cuda", generator=g)
+    far = torch.empty(98, (1 << 31) // (98 * 4) + 1, device="cuda")
+    far[:, :n] = P
+    dp, dm = gs.emission_backward(P, mean, rx, tx, up)
+    dpf, dmf = gs.emission_backward(far, mean, rx, tx, up)
+    torch.cuda.synchronize()
+    assert float((dp - dpf[:, :n]).abs().max()) <= 1e-5 * float(dp.abs().max())
+    assert float((dm - dmf).abs().max()) <= 1e-5 * float(dm.abs().max())
