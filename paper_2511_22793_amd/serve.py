@@ -176,7 +176,8 @@ class Autotuner:
     persistent workgroups.
 
     Per job signature (Gaussian count, grid, channels): every candidate
-    shape of each class and every channel group dividing F*c is timed on the
+    shape of each class, with the library's own channel grouping and every
+    group dividing F*c, is timed on the
     job's first `probe` receivers as a one-job batch; the best per class is
     kept (cached in `cache`, a JSON file when `path` is given).  The class
     whose summed best times over the batch is smallest wins, then the
@@ -203,7 +204,9 @@ class Autotuner:
             return self.cache[key]
         probe = job.head(self.probe)
         fc = job.F * (2 if job.is_complex else 1)
-        groups = [c for c in CHAN_GROUPS if fc % c == 0] or [fc & -fc if fc & -fc <= 32 else 32]
+        # 0: the library's own choice (every column of a set after one walk);
+        # with a group the walk is repeated per group
+        groups = [0] + ([c for c in CHAN_GROUPS if fc % c == 0] or [fc & -fc if fc & -fc <= 32 else 32])
         res = {}
         for block, shapes in TILE_SHAPES.items():
             best = None
