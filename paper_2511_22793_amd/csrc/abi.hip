@@ -356,8 +356,6 @@ static gs_status render_backward(const gs_scene* scene, const gs_attrs* attrs, c
     const int C = attrs->is_complex ? 2 : 1;
     const size_t na = (size_t)(attrs->query_stride ? n_sets : 1) * scene->n * attrs->n_chan * C;
     launch_fill_u32((uint32_t*)(ws + L.g2d), (size_t)L.n * 8, L.s_g2d / 4, L.nq, 0u, s);
-    // the per-pair accumulator over the walked entries (the fold clears it again)
-    launch_geo_clear(L, ws, s);
     if (!(flags & GS_BWD_ATTR_GRAD_ZEROED)) launch_fill_u32((uint32_t*)d_attr, na, 0, 1, 0u, s);
     st = launch_blend_bwd(*attrs, *prm, L, n_sets, ws, spectrum, up, d_attr, s);
     if (st != GS_OK) return st;

@@ -15,11 +15,11 @@
 //
 // Per list entry the per-pixel terms are summed over the wave by a
 // butterfly reduce-scatter (every lane ends with one summed value) and leave
-// by atomics: geometric terms into a per-pair accumulator (only the
-// workgroups of one tile share an address) that a second pass folds into the
-// per-Gaussian sums, attribute gradients into the Gaussian's row.  The
-// nearest Gaussians cover every tile, so per-Gaussian geometric atomics
-// would serialise on a few addresses.
+// by atomics into a per-pair accumulator (only the workgroups of one tile
+// share an address) that a second pass folds into the per-Gaussian sums and
+// the attribute gradients.  The nearest Gaussians cover every tile, so
+// per-Gaussian atomics of every 64 pixels would serialise on a few addresses
+// and add thousands of terms to one running FP32 sum.
 #include <type_traits>
 
 #include "common.h"
@@ -72,6 +72,34 @@ __device__ __forceinline__ void wave_reduce_scatter8(float* x, int lane)
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// Where the attribute gradients of a tile's entries are summed over the tile
+// before they go to the Gaussians' rows (pair: the tile's part of the
+// per-pair accumulator, 8 floats per list entry, of which the first m entries
+// are walked and hold their geometric terms).
+//   one value per entry: slot 7 of its 8 floats (the geometric terms are seven)
+//   `row` values: behind the walked entries' terms, as many entries from the
+//   front as the unwalked ones leave room for; the entries behind those add
+//   straight to the Gaussians' rows.  Lists are mostly far longer than their
+//   walks (thousands against tens), so that is rare; the front entries, the
+//   nearest Gaussians, are those that most tiles add to.
+// 12,000 Gaussians, 16 receivers of one channel at 45 x 180: rms error of the
+// attribute gradients 2.2e-7 against 64 bits with every 64 pixels added
+// straight, 1.05e-7 so; 50,000 Gaussians at 90 x 360: 484 us a fit either way.
+struct PairAttr {
+    int row;    // values per entry over all sets that share the accumulator; 0: none
+    int slot7;  // the one value is in slot 7
+    __device__ uint32_t entries(uint32_t m, uint32_t len) const
+    {
+        if (slot7) return m;
+        const unsigned long long room = (unsigned long long)(len - m) * 8u;
+        return row ? (uint32_t)min((unsigned long long)m, room / (uint32_t)row) : 0u;
+    }
+    __device__ size_t at(uint32_t m, uint32_t e) const
+    {
+        return slot7 ? (size_t)e * 8 + 7 : (size_t)m * 8 + (size_t)e * (uint32_t)row;
+    }
+};
+
 constexpr int BWD_WAVES = 4;                      // waves that share 64 pixels
 constexpr int BWD_SUB = WALK_BATCH / BWD_WAVES;   // entries of a batch per wave, at most
 
@@ -92,8 +120,7 @@ struct alignas(16) BwdRec {
 // quarter of those that reach it, forms the transmittance product and the
 // prefix sum P of its quarter, and after one exchange knows T and P in front
 // of it (P = P_0 + T_0 P_local).  The sums go to memory by atomics straight
-// from the wave: geometric terms into the pair's row (only the workgroups of
-// one tile share it), attribute gradients into the Gaussian's.
+// from the wave, into the pair's row (PairAttr: attribute gradients too).
 // CG >= 16: gv = v . g per (entry, pixel) and the attribute gradient
 // dA[e][f] = sum_p w[p][e] g[p][f] are products on the FP32 matrix cores
 // (v_mfma_f32_16x16x4_f32), with g and w in LDS; smaller groups reduce over
@@ -108,7 +135,8 @@ __global__ __launch_bounds__(64 * BWD_WAVES) __attribute__((amdgpu_waves_per_eu(
     int Fc, int C, int H, int W, int tw, int th, int TX, float amin, float amax,
     const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ tgt,
     const float* __restrict__ mgrad, float gscale, const uint32_t* __restrict__ n_last, size_t s_pix,
-    float* __restrict__ gacc, size_t s_gacc, float* __restrict__ d_attr, int64_t da_stride, int shared_geo)
+    float* __restrict__ gacc, size_t s_gacc, float* __restrict__ d_attr, int64_t da_stride, int shared_geo,
+    PairAttr pa)
 {
     constexpr bool MFMA = CG >= 16;
     constexpr int NB = MFMA ? CG / 16 : 1;
@@ -143,11 +171,27 @@ __global__ __launch_bounds__(64 * BWD_WAVES) __attribute__((amdgpu_waves_per_eu(
     __shared__ float s_w[MFMA ? BWD_WAVES : 1][MFMA ? BWD_SUB : 1][65];
 
     const uint32_t stop = inside ? n_last[q * s_pix + pix] : 0u;
-    uint32_t nent = stop;  // the walk ends at the largest stop position
+    // the walk ends at the largest stop position of the pixels; m: of the tile's
+    uint32_t nent, m = 0u;
+    {
+        __shared__ uint32_t s_m[BWD_WAVES];
+        const int tt = threadIdx.x, tc = txi * tw + tt % tw, tr = tyi * th + tt / tw;
+        uint32_t x = tt < tw * th && tc < W && tr < H ? n_last[q * s_pix + (size_t)tr * W + tc] : 0u;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nent = max(nent, (uint32_t)__shfl_xor((int)nent, o, 64));
-    nent = __builtin_amdgcn_readfirstlane(nent);
+        for (int o = 32; o > 0; o >>= 1) x = max(x, (uint32_t)__shfl_xor((int)x, o, 64));
+        if (lane == 0) s_m[wave] = x;
+        __syncthreads();
+        nent = __builtin_amdgcn_readfirstlane(s_m[box_i]);
+#pragma unroll
+        for (int w = 0; w < BWD_WAVES; ++w) m = max(m, s_m[w]);
+        m = __builtin_amdgcn_readfirstlane(min(m, rg.y - rg.x));
+    }
     if (nent == 0) return;
+    const uint32_t na = pa.entries(m, rg.y - rg.x);
+    // the first channel of the group in entry 0's row, and the floats from
+    // one entry's to the next
+    float* const pv = gacc + pa.at(m, 0) + (shared_geo && da_stride ? (size_t)set * Fc : 0) + ch0;
+    const uint32_t pstep = pa.slot7 ? 8u : (uint32_t)pa.row;
 
     // dL/dout of the pixel's channel ch0 + k: the elementwise part (read, or
     // formed from the output and the target) + the set's channel-mean term;
@@ -348,7 +392,7 @@ __global__ __launch_bounds__(64 * BWD_WAVES) __attribute__((amdgpu_waves_per_eu(
             if (__ballot(any) == 0ull) continue;
             const BwdRec& be = s_ent[wave][min(j + (lane & (BWD_STEP - 1)), cnt - 1)];
             const uint32_t pos = be.pos;
-            float* const dv = dA + (size_t)be.g * Fc;
+            auto attr_row = [&]() { return pos < na ? pv + (size_t)pos * pstep : dA + (size_t)be.g * Fc; };
             float v = 0.0f;
 #pragma unroll
             for (int i = 0; i < BWD_STEP; ++i) {
@@ -357,7 +401,7 @@ __global__ __launch_bounds__(64 * BWD_WAVES) __attribute__((amdgpu_waves_per_eu(
             }
             if (v != 0.0f) {
                 float* p = gacc + (size_t)pos * 8 + (lane >> 3);
-                if (CG == 1 && lane >= 56) p = dv;
+                if (CG == 1 && !pa.slot7 && lane >= 56) p = attr_row();
                 unsafeAtomicAdd(p, v);
             }
             if constexpr (!MFMA && CG > 1) {
@@ -371,7 +415,7 @@ __global__ __launch_bounds__(64 * BWD_WAVES) __attribute__((amdgpu_waves_per_eu(
                     wave_reduce_scatter<CG>(red, lane);
                     v = (lane & ((1 << shA) - 1)) == i ? red[0] : v;
                 }
-                if (v != 0.0f && (lane >> shA) < nch) unsafeAtomicAdd(dv + (lane >> shA), v);
+                if (v != 0.0f && (lane >> shA) < nch) unsafeAtomicAdd(attr_row() + (lane >> shA), v);
             }
         }
         if constexpr (MFMA) {
@@ -379,23 +423,36 @@ __global__ __launch_bounds__(64 * BWD_WAVES) __attribute__((amdgpu_waves_per_eu(
                 // (rows behind cnt hold what the first product left; their
                 // sums are not used)
                 walk_wave_sync();
-                f32x4 acc[NB];
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                // (in CH chains of 16 / CH steps that are then added, as many
+                // as the registers hold: one chain rounds as often as the
+                // sum over the pixels is long)
+                constexpr int CH = NB == 1 ? 8 : (NB == 2 ? 4 : 2);
+                f32x4 part[CH][NB], acc[NB];
 #pragma unroll
                 for (int st = 0; st < 16; ++st) {
                     const float a = s_w[wave][lane & 15][4 * st + (lane >> 4)];
+                    const int h = st % CH;
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                            a, s_g[16 * nb + (lane & 15)][4 * st + (lane >> 4)], acc[nb], 0, 0, 0);
+                        part[h][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            a, s_g[16 * nb + (lane & 15)][4 * st + (lane >> 4)],
+                            st < CH ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : part[h][nb], 0, 0, 0);
+                }
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+                    for (int d = 1; d < CH; d *= 2)
+#pragma unroll
+                        for (int h = 0; h < CH; h += 2 * d) part[h][nb] += part[h + d][nb];
+                    acc[nb] = part[0][nb];
                 }
                 // lane holds entries 4 (lane / 16) + r, channel 16 nb + lane % 16
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr) {
                     const int e = 4 * (lane >> 4) + rr;
                     if (e < cnt) {
-                        float* p = dA + (size_t)s_ent[wave][e].g * Fc + (lane & 15);
+                        const BwdRec& be = s_ent[wave][e];
+                        float* p = (be.pos < na ? pv + (size_t)be.pos * pstep : dA + (size_t)be.g * Fc) + (lane & 15);
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb)
                             if (acc[nb][rr] != 0.0f && 16 * nb + (lane & 15) < nch) unsafeAtomicAdd(p + 16 * nb, acc[nb][rr]);
@@ -878,18 +935,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // The per-pair accumulator is used over the walked part of each tile's list
 // only, up to the largest stop position of the tile's pixels: tens of
-// entries of lists that run to thousands.  One workgroup per (tile, query)
-// zeroes it (FOLD false, before a backward) or folds it into the
-// per-Gaussian accumulators and clears it again (FOLD true).  Over all pairs
+// entries of lists that run to thousands.  Workgroups of a (tile, query)
+// zero it (FOLD false, before a backward) or fold it into the per-Gaussian
+// accumulators and the attribute gradients and clear it again (FOLD true;
+// blockIdx.z: the geometric terms, then PAIR_COLS columns of the attribute
+// rows each).  Over all pairs
 // these two passes took 30 and 87 us at 6.7 million pairs (300,000 Gaussians,
 // 180 x 720), 16 and 28 us at 2.7 million of 16 receivers; 6 and 13, 5 and
 // 24 us so (the last bound by the atomics of Gaussians that many tiles walk).
+constexpr int PAIR_COLS = 32;
+constexpr int PAIR_ROW_MAX = 1024;  // longer rows hardly fit anywhere, and every PAIR_COLS of them cost a workgroup per tile
+
 template <bool FOLD>
 __global__ __launch_bounds__(256) void k_geo_pairs(float* __restrict__ gacc, size_t s_gacc,
                                                    const uint32_t* __restrict__ plist, size_t s_plist,
                                                    const uint2* __restrict__ ranges, size_t s_ranges,
                                                    const uint32_t* __restrict__ n_last, size_t s_pix, int H, int W,
-                                                   int tw, int th, int TX, float* __restrict__ g2d, size_t s_g2d)
+                                                   int tw, int th, int TX, float* __restrict__ g2d, size_t s_g2d,
+                                                   PairAttr pa, float* __restrict__ d_attr, int64_t da_stride, int Fc)
 {
     const int q = blockIdx.y, tile = blockIdx.x, t = threadIdx.x;
     const int col = tile % TX * tw + t % tw, row = tile / TX * th + t / tw;
@@ -900,45 +963,90 @@ __global__ __launch_bounds__(256) void k_geo_pairs(float* __restrict__ gacc, siz
     if ((t & 63) == 0) s_m[t >> 6] = m;
     __syncthreads();
     const uint2 rg = ranges[q * s_ranges + tile];
-    m = min(max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3])), rg.y - rg.x);
+    const uint32_t len = rg.y - rg.x;
+    m = min(max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3])), len);
+    const uint32_t na = pa.entries(m, len);
     float* acc = gacc + q * s_gacc + (size_t)rg.x * 8;
     if constexpr (!FOLD) {
-        for (uint32_t e = t; e < m * 2u; e += 256) ((float4*)acc)[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        // (the attribute rows end inside the tile's len 8-float rows, also
+        // when rounded up to four floats)
+        const size_t n4 = (size_t)m * 2 + (pa.slot7 ? 0 : ((size_t)na * pa.row + 3) / 4);
+        for (size_t e = t; e < n4; e += 256) ((float4*)acc)[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     } else {
         plist += q * s_plist + rg.x;
-        g2d += q * s_g2d;
-        for (uint32_t e = t; e < m * 8u; e += 256) {
-            const float v = acc[e];
-            if (v != 0.0f) {
-                acc[e] = 0.0f;
-                unsafeAtomicAdd(g2d + (size_t)plist[e / 8] * 8 + (e & 7), v);
+        if (blockIdx.z == 0) {
+            g2d += q * s_g2d;
+            for (uint32_t e = t; e < m * 8u; e += 256) {
+                const float v = acc[e];
+                if (v != 0.0f) {
+                    acc[e] = 0.0f;
+                    const size_t g = plist[e / 8];
+                    float* p = g2d + g * 8 + (e & 7);
+                    if (pa.slot7 && (e & 7) == 7) p = d_attr + q * da_stride + g;
+                    unsafeAtomicAdd(p, v);
+                }
+            }
+            return;
+        }
+        // columns [c0, c0 + nc) of the rows: set c / Fc, channel c % Fc (one
+        // set, or all sets over the one geometry)
+        const int c0 = ((int)blockIdx.z - 1) * PAIR_COLS, nc = min(PAIR_COLS, pa.row - c0);
+        const int k = t % PAIR_COLS, c = c0 + k, s = c / Fc;
+        if (k >= nc) return;
+        float* arow = acc + pa.at(m, 0) + c;
+        float* d = d_attr + (q + s) * da_stride + (c - s * Fc);
+        constexpr int EP = 256 / PAIR_COLS, UN = 4;  // entries per step; steps whose loads go together
+        for (uint32_t e0 = t / PAIR_COLS; e0 < na; e0 += EP * UN) {
+            float v[UN];
+            uint32_t g[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const uint32_t e = e0 + u * EP;
+                v[u] = e < na ? arow[(size_t)e * pa.row] : 0.0f;
+                g[u] = e < na ? plist[e] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                if (v[u] != 0.0f) {
+                    arow[(size_t)(e0 + u * EP) * pa.row] = 0.0f;
+                    unsafeAtomicAdd(d + (size_t)g[u] * Fc, v[u]);
+                }
             }
         }
     }
 }
 
 template <bool FOLD>
-static void launch_geo_pairs(const Layout& L, char* ws, hipStream_t s)
+static void launch_geo_pairs(const Layout& L, char* ws, PairAttr pa, float* d_attr, int64_t da_stride, int Fc,
+                             hipStream_t s)
 {
-    hipLaunchKernelGGL(k_geo_pairs<FOLD>, dim3(L.T, L.nq), dim3(256), 0, s, (float*)(ws + L.gacc), L.s_gacc / 4,
+    const int z = FOLD && !pa.slot7 ? 1 + (pa.row + PAIR_COLS - 1) / PAIR_COLS : 1;
+    hipLaunchKernelGGL(k_geo_pairs<FOLD>, dim3(L.T, L.nq, z), dim3(256), 0, s, (float*)(ws + L.gacc), L.s_gacc / 4,
                        (const uint32_t*)(ws + L.plist), L.s_plist / 4, (const uint2*)(ws + L.ranges),
                        L.s_ranges / sizeof(uint2), (const uint32_t*)(ws + L.n_last), L.s_pix / 4, L.H, L.W, L.tw,
-                       L.th, L.TX, (float*)(ws + L.g2d), L.s_g2d / 4);
+                       L.th, L.TX, (float*)(ws + L.g2d), L.s_g2d / 4, pa, d_attr, da_stride, Fc);
 }
 
-void launch_geo_clear(const Layout& L, char* ws, hipStream_t s) { launch_geo_pairs<false>(L, ws, s); }
-void launch_geo_fold(const Layout& L, char* ws, hipStream_t s) { launch_geo_pairs<true>(L, ws, s); }
+void launch_geo_clear(const Layout& L, char* ws, hipStream_t s)
+{
+    launch_geo_pairs<false>(L, ws, PairAttr{0, 0}, nullptr, 0, 1, s);
+}
+void launch_geo_fold(const Layout& L, char* ws, hipStream_t s)
+{
+    launch_geo_pairs<true>(L, ws, PairAttr{0, 0}, nullptr, 0, 1, s);
+}
 
 template <int CG>
 static void bwd_cg(dim3 grid, dim3 block, hipStream_t s, const gs_attrs& a, const gs_params& p, const Layout& L,
-                   char* ws, const float* out, const BwdUpstream& up, float* d_attr, int64_t da_stride, int C, int shared)
+                   char* ws, const float* out, const BwdUpstream& up, float* d_attr, int64_t da_stride, int C, int shared,
+                   PairAttr pa)
 {
     hipLaunchKernelGGL(k_blend_bwd<CG>, grid, block, 0, s, (const GRec*)(ws + L.rec), L.s_rec / sizeof(GRec),
                        (const uint32_t*)(ws + L.plist), L.s_plist / 4, (const uint2*)(ws + L.ranges),
                        L.s_ranges / sizeof(uint2), a.data, a.query_stride, a.n_chan * C, C, L.H, L.W, L.tw, L.th,
                        L.TX, p.alpha_min, p.alpha_max, out, up.dout, up.target, up.mean_grad, up.scale,
                        (const uint32_t*)(ws + L.n_last), L.s_pix / 4,
-                       (float*)(ws + L.gacc), L.s_gacc / 4, d_attr, da_stride, shared);
+                       (float*)(ws + L.gacc), L.s_gacc / 4, d_attr, da_stride, shared, pa);
 }
 
 // k_blend_bwd_sg with g = scale (out - target) + mean_grad over the groups
@@ -967,6 +1075,8 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
     const int Fc = a.n_chan * C;
     // (32-bit element offsets inside one set's spectrum)
     const bool offs32 = (uint64_t)Fc * L.H * L.W < (1ull << 30);
+    const int64_t das = a.query_stride;  // d_attr mirrors the attribute layout
+    PairAttr pa{0, 0};
     if (L.nq == 1 && Fc % 16 == 0 && offs32 && !(p.options & GS_OPT_BWD_PER_GROUP)) {
         // one geometry for every set: the factorised backward
         int tw_log = 0;
@@ -974,6 +1084,7 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
         const SgUp sup{out, up.dout, up.target, up.mean_grad, up.scale, nullptr};
         const dim3 grid(L.T, (L.tw * L.th) / SG_PIX), block(SG_WAVES * 64);
         void* tok;
+        launch_geo_pairs<false>(L, ws, pa, d_attr, das, Fc, s);
         timing_begin(TK_BLEND_BWD, s, &tok);
         auto kern = C == 2 ? (up.target ? k_blend_bwd_sg<1, true> : k_blend_bwd_sg<1, false>)
                            : (up.target ? k_blend_bwd_sg<0, true> : k_blend_bwd_sg<0, false>);
@@ -994,21 +1105,24 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
     if (ngr > 65535) return GS_ERR_CAPACITY;
     const int shared = (L.nq == 1 && n_sets > 1) ? 1 : 0;
     dim3 grid(L.T * ((L.tw * L.th) >> 6), ngr, n_sets), block(64 * BWD_WAVES);
-    const int64_t das = a.query_stride;  // d_attr mirrors the attribute layout
+    const int64_t row = shared && das ? (int64_t)Fc * n_sets : Fc;
+    pa.slot7 = row == 1;
+    pa.row = row <= PAIR_ROW_MAX ? (int)row : 0;
+    launch_geo_pairs<false>(L, ws, pa, d_attr, das, Fc, s);
     void* tok;
     timing_begin(TK_BLEND_BWD, s, &tok);
     switch (cg) {
-        case 1: bwd_cg<1>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
-        case 2: bwd_cg<2>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
-        case 4: bwd_cg<4>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
-        case 8: bwd_cg<8>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
-        case 16: bwd_cg<16>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
-        case 32: bwd_cg<32>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
-        default: bwd_cg<64>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared); break;
+        case 1: bwd_cg<1>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared, pa); break;
+        case 2: bwd_cg<2>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared, pa); break;
+        case 4: bwd_cg<4>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared, pa); break;
+        case 8: bwd_cg<8>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared, pa); break;
+        case 16: bwd_cg<16>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared, pa); break;
+        case 32: bwd_cg<32>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared, pa); break;
+        default: bwd_cg<64>(grid, block, s, a, p, L, ws, out, up, d_attr, das, C, shared, pa); break;
     }
     timing_end(tok, s);
     }
-    launch_geo_fold(L, ws, s);
+    launch_geo_pairs<true>(L, ws, pa, d_attr, das, Fc, s);
     return GS_OK;
 }
 
