@@ -142,15 +142,18 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW
     }
     for (uint32_t b0 = 0; b0 < len; b0 += WALK_BATCH) {
         int slot;
-        bool plain;
+        bool plain, odd = false;  // odd: a queued entry has a value that is not finite
         const int m = walk_queue(S.Q, r_next, g_next, b0 + lane + 1, b0 + lane < len, box, Wd, amin, lane, slot, plain);
         if constexpr (!MF) {
             const bool pad = lane >= m && lane < (m + WALK_STEP - 1) / WALK_STEP * WALK_STEP;
+            float z = 0.0f;
 #pragma unroll
             for (int k = 0; k < CG; ++k) {
                 if (slot >= 0) S.u.v[slot][k] = v_next[k];
                 if (pad) S.u.v[lane][k] = 0.0f;
+                z = fmaf(v_next[k], 0.0f, z);
             }
+            odd = __ballot(slot >= 0 && z != 0.0f) != 0ull;
         }
         if (b0 + WALK_BATCH < len) {
             g_next = g_after;
@@ -158,8 +161,8 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW
             fetch();
         }
         wave_sync_lds();
-        auto walk = [&](auto pl) {
-            constexpr bool PLAIN = decltype(pl)::value;
+        auto walk = [&](auto pl, auto od) {
+            constexpr bool PLAIN = decltype(pl)::value, ODD = decltype(od)::value;
             if constexpr (MF) {
                 for (int j0 = 0; j0 < m; j0 += 16) {
                     if (walk_done(px)) break;  // all the wave's pixels stopped
@@ -187,6 +190,30 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW
                         steps = ks + 1;
                     }
                     wave_sync_lds();
+                    float z = 0.0f;
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) z = fmaf(bv[ks][nb], 0.0f, z);
+                    if (__ballot(z != 0.0f) != 0ull) {
+                        // entry by entry, where it weighs
+                        for (int r = 0; r < WALK_STEP * steps && j0 + r < m; ++r) {
+                            const CFloat* vr = (const CFloat*)(A + (size_t)S.Q.g[j0 + r] * Fc + (lane & 15));
+#pragma unroll
+                            for (int nb = 0; nb < NB; ++nb) {
+                                const float v = 16 * nb + (lane & 15) < chn ? vr[16 * nb] : 0.0f;
+#pragma unroll
+                                for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+                                    for (int i = 0; i < 4; ++i) {
+                                        const float w = S.u.w[r][16 * pb + 4 * (lane >> 4) + i];
+                                        macc[pb][nb][i] = w != 0.0f ? fmaf(w, v, macc[pb][nb][i]) : macc[pb][nb][i];
+                                    }
+                            }
+                        }
+                        wave_sync_lds();
+                        continue;
+                    }
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks) {
                         if (ks < steps) {
@@ -211,12 +238,16 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW
 #pragma unroll
                     for (int i = 0; i < WALK_STEP; ++i)
 #pragma unroll
-                        for (int k = 0; k < CG; ++k) acc[k] = fmaf(w[i], S.u.v[j + i][k], acc[k]);
+                        for (int k = 0; k < CG; ++k) {
+                            const float x = fmaf(w[i], S.u.v[j + i][k], acc[k]);
+                            acc[k] = !ODD || w[i] != 0.0f ? x : acc[k];
+                        }
                 }
             }
         };
-        if (plain) walk(std::true_type{});
-        else walk(std::false_type{});
+        if (!MF && odd) walk(std::false_type{}, std::true_type{});
+        else if (plain) walk(std::true_type{}, std::false_type{});
+        else walk(std::false_type{}, std::false_type{});
         if (walk_done(px)) break;
         wave_sync_lds();  // the next batch reuses the queue
     }
@@ -418,9 +449,12 @@ struct MxOut {
 // outside the image, and the rows past the buffered steps, go past the
 // buffers' range (reads give 0).  NV = 2: complex columns, 32 a block.
 // Loads wait in issue order behind the stores before them, so a block's are
-// issued ahead of the previous block's stores.
+// issued ahead of the previous block's stores.  NV = 1: returns the first
+// block with a value that is not finite, which is left to mx_products_big with
+// those behind it (a zero weight takes such a value to every pixel of the
+// wave, also to those that stopped in front of it); else cb_hi.
 template <int NV, int NS>
-__device__ __forceinline__ void mx_products(const MxOut& O, const MxWave& S, int steps, bool stored, int cb_lo, int cb_hi)
+__device__ __forceinline__ int mx_products(const MxOut& O, const MxWave& S, int steps, bool stored, int cb_lo, int cb_hi)
 {
     const int lane = threadIdx.x & 63, j4 = lane >> 4, l16 = lane & 15;
     const uint32_t HW4 = (uint32_t)O.HW * 4u;  // bytes of a column's plane (of a pair's: 2 HW4)
@@ -491,8 +525,16 @@ __device__ __forceinline__ void mx_products(const MxOut& O, const MxWave& S, int
 #pragma unroll
                 for (int pb = 0; pb < 4; ++pb)
                     acc[v][pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][v], wB[ks][pb], acc[v][pb], 0, 0, 0);
+        bool odd = false;  // a value that is not finite
+        if constexpr (NV == 1) {
+            float z = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < NS; ++ks) z = fmaf(av[ks][0], 0.0f, z);
+            odd = __ballot(z != 0.0f) != 0ull;
+        }
         if (cb + 1 < cb_hi) load(cb + 1);
         __builtin_amdgcn_sched_barrier(0);
+        if (odd) return cb;
         // the value of column offset e, in column order
         auto val = [&](int pb, int e) { return __float_as_uint(acc[e % NV][pb][e / NV]); };
         if (NV > 1 || O.cs) {
@@ -510,10 +552,12 @@ __device__ __forceinline__ void mx_products(const MxOut& O, const MxWave& S, int
                 for (int pb = 0; pb < 4; ++pb) __builtin_amdgcn_raw_buffer_store_b32(val(pb, e), r, at(e, pb), 0, MX_NT);
         }
     }
+    return cb_hi;
 }
 
-// The same in 64-bit addressing, for attributes or spectra past 2 GiB a set
-// and for complex spectra that are not 8-byte aligned.
+// The same in 64-bit addressing, for attributes or spectra past 2 GiB a set,
+// for complex spectra that are not 8-byte aligned and for blocks with values
+// that are not finite: those entries are added where they weigh only.
 __device__ __forceinline__ void mx_products_big(const MxOut& O, const MxWave& S, int steps, bool stored, int cb_lo,
                                                 int cb_hi)
 {
@@ -538,6 +582,21 @@ __device__ __forceinline__ void mx_products_big(const MxOut& O, const MxWave& S,
 #pragma unroll 1
         for (int ks = 0; ks < steps; ++ks) {
             const float a = c0 + l16 < O.Fc ? vb[(size_t)S.g[WALK_STEP * ks + j4] * O.Fc] : 0.0f;
+            if (__ballot(a * 0.0f != 0.0f) != 0ull) {
+                for (int k = WALK_STEP * ks; k < WALK_STEP * (ks + 1); ++k) {
+                    const CFloat* vr = (const CFloat*)(O.attr + s * O.a_stride + (size_t)S.g[k] * O.Fc + c);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float v = c + i < O.Fc ? vr[i] : 0.0f;
+#pragma unroll
+                        for (int pb = 0; pb < 4; ++pb) {
+                            const float wk = S.w[k][4 * l16 + pb];
+                            acc[pb][i] = wk != 0.0f ? fmaf(wk, v, acc[pb][i]) : acc[pb][i];
+                        }
+                    }
+                }
+                continue;
+            }
             const float4 w = *(const float4*)&S.w[WALK_STEP * ks + j4][4 * l16];
             acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w.x, acc[0], 0, 0, 0);
             acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w.y, acc[1], 0, 0, 0);
@@ -631,12 +690,18 @@ __device__ __forceinline__ void blend_mx_unit(const BlendJob& J, MxWave& S, int 
                 continue;
             }
             float w[WALK_STEP];
+            const uint32_t gq = S.Q.g[j + (lane & (WALK_STEP - 1))];
             if (plain) walk_step<true>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
             else walk_step<false>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
-            if (__ballot(w[0] != 0.0f || w[1] != 0.0f || w[2] != 0.0f || w[3] != 0.0f) != 0ull) {
+            uint32_t any = 0u;  // the step's entries that weigh at some pixel
+#pragma unroll
+            for (int i = 0; i < WALK_STEP; ++i) any |= __ballot(w[i] != 0.0f) != 0ull ? 1u << i : 0u;
+            if (any) {
 #pragma unroll
                 for (int i = 0; i < WALK_STEP; ++i) S.w[WALK_STEP * steps + i][4 * l16 + j4] = w[i];
-                if (lane < WALK_STEP) S.g[WALK_STEP * steps + lane] = S.Q.g[j + lane];
+                // (an entry that weighs nowhere goes with another's values)
+                const uint32_t g1 = __builtin_amdgcn_readlane(gq, __ffs(any) - 1);
+                if (lane < WALK_STEP) S.g[WALK_STEP * steps + lane] = any >> lane & 1u ? gq : g1;
                 ++steps;
             }
             j += WALK_STEP;
@@ -652,10 +717,12 @@ __device__ __forceinline__ void blend_mx_unit(const BlendJob& J, MxWave& S, int 
         if constexpr (BIG) {
             mx_products_big(O, S, steps, stored, cb_lo, cb_hi);
         } else {
-            if (ns == 4) mx_products<NV, 4>(O, S, steps, stored, cb_lo, cb_hi);
-            else if (ns == 8) mx_products<NV, 8>(O, S, steps, stored, cb_lo, cb_hi);
-            else if (ns == 12) mx_products<NV, 12>(O, S, steps, stored, cb_lo, cb_hi);
-            else mx_products<NV, 16>(O, S, steps, stored, cb_lo, cb_hi);
+            int cb;
+            if (ns == 4) cb = mx_products<NV, 4>(O, S, steps, stored, cb_lo, cb_hi);
+            else if (ns == 8) cb = mx_products<NV, 8>(O, S, steps, stored, cb_lo, cb_hi);
+            else if (ns == 12) cb = mx_products<NV, 12>(O, S, steps, stored, cb_lo, cb_hi);
+            else cb = mx_products<NV, 16>(O, S, steps, stored, cb_lo, cb_hi);
+            if (NV == 1 && cb < cb_hi) mx_products_big(O, S, steps, stored, cb, cb_hi);
         }
         stored = true;
         steps = 0;
