@@ -46,15 +46,15 @@ __device__ __forceinline__ float adam_one(float p, float g, float& m, float& v, 
     v = (float)vd;
     // square root and reciprocal from the hardware estimates (about 24 bits)
     // and one Newton step each: 48 bits, and no scaling sequences.  A
-    // second moment that overflowed to infinity makes no update, as a finite
-    // bound that the Newton steps can take
-    double x = vd * K.ic2;
-    x = x > 1e300 ? 1e300 : x;
+    // second moment that overflowed to infinity divides to 0 (which the
+    // Newton steps would not reach): no update, or NaN where the first
+    // moment is infinite too
+    const double x = vd * K.ic2;
     double y = __builtin_amdgcn_rsq(x);
     y = y * fma(-0.5 * x * y, y, 1.5);
     const double den = (x > 0.0 ? x * y : x) + K.eps;
     double r = __builtin_amdgcn_rcp(den);
-    r = fma(r, fma(-den, r, 1.0), r);
+    r = x == (double)INFINITY ? 0.0 : fma(r, fma(-den, r, 1.0), r);
     return (float)(p - (K.lr * K.ic1) * md * r);
 }
 
