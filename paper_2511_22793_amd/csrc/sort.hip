@@ -336,19 +336,23 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_
 // these sizes the launches and their latency are the time (2,000 keys: 35 us
 // in 8 launches by the radix sort, 6 us so; 100,000: 48 and 28 us; 300,000:
 // 64 us in 12 launches and 40 us).
-// Beyond DS_MAX the 1024 bins (512 keys on average there, a largest of 4 times
-// that with 4 samples per bin) outgrow a workgroup's registers.  A bin that
-// the samples missed and that does not fit (the places are known, so one can
-// be built) is sorted in place in global memory by its workgroup: slow, but
-// right.
+// With 4 samples per bin a bin's size is close to a gamma variable of shape 4:
+// 1024 bins of 512 keys on average, at DS_MAX, have one of more than 2048 in
+// 8 sorts of 100, one of more than 4096 in 1e-7.  A workgroup takes up to 4096
+// (DS_CAP) in its registers; beyond DS_MAX the bins outgrow that.  With 2048 as
+// the limit 16 receivers of 524,288 Gaussians prepared in 1.11 ms, or in 2.00
+// where a bin was larger (1.28 now; 1.58 by the radix sort).  A larger bin (the
+// samples' places are known, so one can be built) is sorted in place in
+// global memory by its workgroup: slow, but right.
 constexpr int DS_ONE = 4096;
 constexpr int DS_MAX = 1 << 19;
 constexpr int DS_MAX_BINS = 1024; // words of a query's totals
 constexpr int DS_BIN = 320;       // keys per bin aimed at
 constexpr int DS_OVER = 4;        // samples per bin
 constexpr int DS_RANK = 32;       // elements ranked per workgroup
-constexpr int DS_WAVES = 4;       // waves that sort a bin, 2, 4 or 8 keys per thread
-constexpr int DS_CAP = 64 * 8 * DS_WAVES;
+constexpr int DS_WAVES = 4;       // waves that sort a bin, 2, 4, 8 or 16 keys per thread
+constexpr int DS_CAP = 64 * 16 * DS_WAVES;
+constexpr int DS_XCHG = 8;        // keys per thread that the exchange between waves holds at once
 
 static int depth_bins(int n)
 {
@@ -402,7 +406,8 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t x)
 // element E tid + i ends in v[i] of thread tid.  A bitonic network whose
 // comparators all point upwards (the first stage of each merge mirrors):
 // inside a thread by registers, between lanes by lane permutations, between
-// waves through LDS (x: 64 NW E elements).
+// waves through LDS (x: 64 NW min(E, DS_XCHG) elements, in as many turns as E
+// takes).
 template <int NW, int E, int K, int J>
 __device__ __forceinline__ void sort_stage(DsKey* v, int tid, DsKey* x)
 {
@@ -428,12 +433,16 @@ __device__ __forceinline__ void sort_stage(DsKey* v, int tid, DsKey* x)
             for (int i = 0; i < E; ++i)
                 p[i] = ((DsKey)lane_xor<tm>((uint32_t)(v[i ^ rm] >> 32)) << 32) | lane_xor<tm>((uint32_t)v[i ^ rm]);
         } else {
-            __syncthreads();
+            constexpr int X = E < DS_XCHG ? E : DS_XCHG;
 #pragma unroll
-            for (int i = 0; i < E; ++i) x[i * NT + tid] = v[i];
-            __syncthreads();
+            for (int i0 = 0; i0 < E; i0 += X) {
+                __syncthreads();
 #pragma unroll
-            for (int i = 0; i < E; ++i) p[i] = x[(i ^ rm) * NT + (tid ^ tm)];
+                for (int i = 0; i < X; ++i) x[i * NT + tid] = v[i0 + i];
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < X; ++i) p[(i0 + i) ^ rm] = x[i * NT + (tid ^ tm)];
+            }
         }
 #pragma unroll
         for (int i = 0; i < E; ++i) v[i] = (p[i] < v[i]) == low ? p[i] : v[i];
@@ -639,7 +648,7 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_depth_local(uint32_t* kin, ui
 {
     constexpr int NT = 64 * DS_WAVES;
     const int q = blockIdx.y, bin = blockIdx.x;
-    __shared__ DsKey x[DS_CAP];
+    __shared__ DsKey x[NT * DS_XCHG];
     const uint32_t m = tot[q * s_tot + bin];
     if (m == 0) return;
     uint32_t pre = 0u;
@@ -661,8 +670,12 @@ __global__ __launch_bounds__(64 * DS_WAVES) void k_depth_local(uint32_t* kin, ui
         sort_run<DS_WAVES, 4>(kin, val, kout, val, m, threadIdx.x, x);
         return;
     }
-    if (m <= (uint32_t)DS_CAP) {
+    if (m <= NT * 8u) {
         sort_run<DS_WAVES, 8>(kin, val, kout, val, m, threadIdx.x, x);
+        return;
+    }
+    if (m <= (uint32_t)DS_CAP) {
+        sort_run<DS_WAVES, 16>(kin, val, kout, val, m, threadIdx.x, x);
         return;
     }
     // the same network on the two arrays in global memory (the missing
