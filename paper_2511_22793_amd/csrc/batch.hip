@@ -87,6 +87,12 @@ static gs_status build_table(const gs_batch_job* jobs, int n_jobs, std::vector<B
     return GS_OK;
 }
 
+// Some job takes the matrix-core form of the compositing.
+static bool any_mx(const std::vector<BlendJob>& table)
+{
+    return std::any_of(table.begin(), table.end(), [](const BlendJob& j) { return j.cg > BLEND_ROW_CG; });
+}
+
 }  // namespace gs
 
 using namespace gs;
@@ -111,7 +117,7 @@ gs_status gs_batch_plan(const gs_batch_job* jobs, int32_t n_jobs, void* plan, si
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return GS_ERR_HIP;
-    if (persist_occupancy(info->block, &per_cu) != hipSuccess) return GS_ERR_HIP;
+    if (persist_occupancy(info->block, any_mx(table), &per_cu) != hipSuccess) return GS_ERR_HIP;
     st = lanes_init(dev);
     if (st != GS_OK) return st;
     info->workgroups = std::max(1, cus * std::max(1, per_cu));
@@ -177,8 +183,8 @@ gs_status gs_batch_run(const gs_batch_job* jobs, int32_t n_jobs, void* plan, siz
         }
     }
     if (ts) launch_stamp(ts + 2 + info.n_queries, s);
-    launch_blend_persist((const BlendJob*)((char*)plan + PLAN_HEAD), n_jobs, (uint32_t)info.items, counter,
-                         ts ? ts + 1 : nullptr, workgroups, info.block, s);
+    launch_blend_persist((const BlendJob*)((char*)plan + PLAN_HEAD), n_jobs, any_mx(table), (uint32_t)info.items,
+                         counter, ts ? ts + 1 : nullptr, workgroups, info.block, s);
     if (ts) launch_stamp(ts + 1 + info.n_queries, s);
     GS_CHECK_LAUNCH();
     return GS_OK;

@@ -791,13 +791,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // out and the matrix-core form's single walk per tile 1.40 ms).
 // Every workgroup exits once its dealt items are done and the counter passes
 // the total.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_blend_persist(
+// MX: some job takes the matrix-core form.  Its 256 registers allow two waves
+// per SIMD and its LDS as many (20 KB a wave); a batch without such a job runs
+// without either (8 KB a wave, four waves per SIMD).  The LDS is sized by the
+// waves launched (persist_lds): with four waves' worth whatever the workgroup,
+// workgroups of 64 and 128 threads ran 2 and 4 waves per CU (4 jobs of 50,000
+// Gaussians, 8 receivers, 16 complex channels: 1036 -> 708 us in 8 x 8 tiles,
+// 756 -> 642 in 8 x 16; one channel: 820 -> 685, 613 -> 516 and 443 -> 416 us
+// in 8 x 8, 8 x 16 and 16 x 16).
+union PersistLds {
+    BlendWave v;
+    MxWave m;
+};
+
+__host__ __device__ constexpr size_t persist_lds(bool mx) { return mx ? sizeof(PersistLds) : sizeof(BlendWave); }
+
+template <bool MX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MX ? 2 : 4))) void k_blend_persist(
     const BlendJob* __restrict__ jobs, int njobs, uint32_t total, uint32_t* counter, unsigned long long* done_ts)
 {
-    __shared__ union PersistLds {
-        BlendWave v[4];
-        MxWave m[4];
-    } S;
+    extern __shared__ __align__(16) char s_waves[];
+    BlendWave* const SV = (BlendWave*)s_waves;
     __shared__ uint32_t s_item[2];
     const int lane = threadIdx.x & 63;
     const uint32_t rounds = (total - total / 4) / gridDim.x, dealt = rounds * gridDim.x;
@@ -835,22 +849,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         const uint32_t rest = local / (uint32_t)J.T;
         const int cg = (int)(rest % (uint32_t)J.ncg);
         const int set = (int)(rest / (uint32_t)J.ncg);
-        if (J.cg > BLEND_ROW_CG) {
-            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-            const int nb = (J.Fc + 16 * J.nv - 1) / (16 * J.nv);
-            const int cb_lo = cg * nb / J.ncg, cb_hi = (cg + 1) * nb / J.ncg;
-#define MX_ARGS J, S.m[wave], tile, wave, set, cb_lo, cb_hi, cg == 0, J.rec, J.plist, J.ranges, J.attr, J.out, J.T_final, \
-                J.n_last, J.n_contrib, 0
-            if (J.big) blend_mx_unit<1, true>(MX_ARGS);
-            else if (J.nv > 1) blend_mx_unit<MX_WIDE, false>(MX_ARGS);
-            else blend_mx_unit<1, false>(MX_ARGS);
+        bool row = true;
+        if constexpr (MX) {
+            row = J.cg <= BLEND_ROW_CG;
+            if (!row) {
+                const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+                const int nb = (J.Fc + 16 * J.nv - 1) / (16 * J.nv);
+                const int cb_lo = cg * nb / J.ncg, cb_hi = (cg + 1) * nb / J.ncg;
+#define MX_ARGS J, ((MxWave*)s_waves)[wave], tile, wave, set, cb_lo, cb_hi, cg == 0, J.rec, J.plist, J.ranges, J.attr, J.out, \
+                J.T_final, J.n_last, J.n_contrib, 0
+                if (J.big) blend_mx_unit<1, true>(MX_ARGS);
+                else if (J.nv > 1) blend_mx_unit<MX_WIDE, false>(MX_ARGS);
+                else blend_mx_unit<1, false>(MX_ARGS);
 #undef MX_ARGS
-        } else {
+            }
+        }
+        if (row) {
             switch (J.cg) {
-                case 1: blend_tile<1>(J, S.v, tile, cg, set); break;
-                case 2: blend_tile<2>(J, S.v, tile, cg, set); break;
-                case 4: blend_tile<4>(J, S.v, tile, cg, set); break;
-                default: blend_tile<8>(J, S.v, tile, cg, set); break;
+                case 1: blend_tile<1>(J, SV, tile, cg, set); break;
+                case 2: blend_tile<2>(J, SV, tile, cg, set); break;
+                case 4: blend_tile<4>(J, SV, tile, cg, set); break;
+                default: blend_tile<8>(J, SV, tile, cg, set); break;
             }
         }
         // the next item's index (two slots: a wave may still read the other),
@@ -1187,15 +1206,17 @@ void launch_blend_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L
     launch_mx(J, L, s, min_walk);
 }
 
-void launch_blend_persist(const BlendJob* jobs, int njobs, uint32_t total, uint32_t* counter,
+void launch_blend_persist(const BlendJob* jobs, int njobs, bool mx, uint32_t total, uint32_t* counter,
                           unsigned long long* done_ts, int workgroups, int block, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_blend_persist, dim3(workgroups), dim3(block), 0, s, jobs, njobs, total, counter, done_ts);
+    hipLaunchKernelGGL(mx ? k_blend_persist<true> : k_blend_persist<false>, dim3(workgroups), dim3(block),
+                       (unsigned)(persist_lds(mx) * (block / 64)), s, jobs, njobs, total, counter, done_ts);
 }
 
-hipError_t persist_occupancy(int block, int* per_cu)
+hipError_t persist_occupancy(int block, bool mx, int* per_cu)
 {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_blend_persist, block, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, mx ? k_blend_persist<true> : k_blend_persist<false>,
+                                                        block, persist_lds(mx) * (block / 64));
 }
 
 void launch_stamp(unsigned long long* ts, hipStream_t s) { hipLaunchKernelGGL(k_stamp, dim3(1), dim3(64), 0, s, ts); }

@@ -196,10 +196,11 @@ struct BlendJob;
 void blend_mx_form(BlendJob* J, int64_t n);
 constexpr int BLEND_ROW_CG = 8;  // channel floats up to which k_blend composites; the matrix-core form beyond
 BlendJob make_blend_job(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out);
-void launch_blend_persist(const BlendJob* jobs, int njobs, uint32_t total, uint32_t* counter,
+// (mx: some job takes the matrix-core form)
+void launch_blend_persist(const BlendJob* jobs, int njobs, bool mx, uint32_t total, uint32_t* counter,
                           unsigned long long* done_ts, int workgroups, int block, hipStream_t s);
 void launch_stamp(unsigned long long* ts, hipStream_t s);
-hipError_t persist_occupancy(int block, int* per_cu);
+hipError_t persist_occupancy(int block, bool mx, int* per_cu);
 // Upstream gradient of the backward: dout alone; or, with mean_grad,
 // dout + mean_grad (dout = the elementwise part of the L2 loss gradient),
 // or scale (out - target) + mean_grad when target is set.
