@@ -690,22 +690,26 @@ __device__ __forceinline__ void blend_mx_unit(const BlendJob& J, MxWave& S, int 
                 continue;
             }
             float w[WALK_STEP];
-            const uint32_t gq = S.Q.g[j + (lane & (WALK_STEP - 1))];
             if (plain) walk_step<true>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
             else walk_step<false>(S.Q, j, px, pcx, pcy, halfW, Wd, amax, tmin, w);
-            uint32_t any = 0u;  // the step's entries that weigh at some pixel
-#pragma unroll
-            for (int i = 0; i < WALK_STEP; ++i) any |= __ballot(w[i] != 0.0f) != 0ull ? 1u << i : 0u;
-            if (any) {
+            if (__ballot(w[0] != 0.0f || w[1] != 0.0f || w[2] != 0.0f || w[3] != 0.0f) != 0ull) {
 #pragma unroll
                 for (int i = 0; i < WALK_STEP; ++i) S.w[WALK_STEP * steps + i][4 * l16 + j4] = w[i];
-                // (an entry that weighs nowhere goes with another's values)
-                const uint32_t g1 = __builtin_amdgcn_readlane(gq, __ffs(any) - 1);
-                if (lane < WALK_STEP) S.g[WALK_STEP * steps + lane] = any >> lane & 1u ? gq : g1;
+                if (lane < WALK_STEP) S.g[WALK_STEP * steps + lane] = S.Q.g[j + lane];
                 ++steps;
             }
             j += WALK_STEP;
             if (walk_done(px)) end = true;
+        }
+        if (end && steps > 0) {
+            // the last step's entries that weigh nowhere (those behind the last
+            // stop) go with the values of one that weighs
+            wave_sync_lds();
+            const int last = WALK_STEP * (steps - 1);
+            uint32_t any = 0u;
+#pragma unroll
+            for (int i = 0; i < WALK_STEP; ++i) any |= __ballot(S.w[last + i][lane] != 0.0f) != 0ull ? 1u << i : 0u;
+            if (lane < WALK_STEP && !(any >> lane & 1u)) S.g[last + lane] = S.g[last + __ffs(any) - 1];
         }
         // the products over the buffered entries, rounded up to a multiple of
         // 4 steps with zero weights (the step count is a constant of each
