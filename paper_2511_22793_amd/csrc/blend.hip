@@ -38,8 +38,8 @@ typedef __attribute__((address_space(4))) const float CFloat;
 // instructions.
 #define GLOBAL_AS __attribute__((address_space(1)))
 
-// LDS of one wave (declared once per kernel, so that the channel-group
-// instantiations of one kernel share it): the queue, and pixel weights of a
+// LDS of one wave (a launch has a slot for each of its waves: tiles of 64 and
+// 128 pixels keep as many waves on a CU as those of 256): the queue, and pixel weights of a
 // run of 16 entries (matrix-core path), the output transpose (64 pixels x
 // 17), or the queued entries' attribute values (up to 8 channels).
 
@@ -374,8 +374,8 @@ __global__ __launch_bounds__(256)
                                                float* __restrict__ T_final, uint32_t* __restrict__ n_last,
                                                uint32_t* __restrict__ n_contrib)
 {
-    __shared__ BlendWave S[4];
-    blend_tile_impl<CG, FUSE>(J, S, blockIdx.x, blockIdx.y, blockIdx.z, rec, plist, ranges, attr, out, T_final,
+    extern __shared__ __align__(16) char s_waves[];  // a BlendWave per wave
+    blend_tile_impl<CG, FUSE>(J, (BlendWave*)s_waves, blockIdx.x, blockIdx.y, blockIdx.z, rec, plist, ranges, attr, out, T_final,
                               n_last, n_contrib);
 }
 
@@ -750,7 +750,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const float* __restrict__ attr, float* __restrict__ out, float* __restrict__ T_final,
     uint32_t* __restrict__ n_last, uint32_t* __restrict__ n_contrib)
 {
-    __shared__ MxWave S[4];
+    extern __shared__ __align__(16) char s_waves[];  // an MxWave per wave
+    MxWave* const S = (MxWave*)s_waves;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = blockIdx.x / J.ncg, cg = blockIdx.x % J.ncg, set = blockIdx.z;
     const int nb = (J.Fc + 16 * NV - 1) / (16 * NV) * (J.across ? J.nsets : 1);
@@ -772,7 +773,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const float* __restrict__ attr, float* __restrict__ out, float* __restrict__ T_final,
     uint32_t* __restrict__ n_last, uint32_t* __restrict__ n_contrib, int items, int min_walk)
 {
-    __shared__ MxWave S[4];
+    extern __shared__ __align__(16) char s_waves[];  // an MxWave per wave
+    MxWave* const S = (MxWave*)s_waves;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nb = (J.Fc + 16 * NV - 1) / (16 * NV) * J.nsets;
     for (int it = blockIdx.x; it < items; it += gridDim.x) {
@@ -1126,6 +1128,7 @@ static gs_status launch_mx(BlendJob J, const Layout& L, hipStream_t s, int min_w
     blend_mx_form(&J, L.n);
     const int nb = (J.Fc + 16 * J.nv - 1) / (16 * J.nv) * (J.across ? J.nsets : 1), z = J.across ? 1 : J.nsets;
     const int gpt = (L.tw * L.th) >> 6;
+    const unsigned lds = (unsigned)(gpt * sizeof(MxWave));
     if (J.ncg == 0) J.ncg = mx_split((int64_t)L.T * gpt * z, nb, J.nv);
     J.ncg = std::min(J.ncg, nb);
     if ((int64_t)L.T * J.ncg > 0x7FFFFFFF) return GS_ERR_CAPACITY;
@@ -1133,12 +1136,12 @@ static gs_status launch_mx(BlendJob J, const Layout& L, hipStream_t s, int min_w
         auto kern = J.big ? k_blend_mx_long<1, true>
                           : (J.nv > 1 ? k_blend_mx_long<MX_WIDE, false> : k_blend_mx_long<1, false>);
         const int items = L.T * J.ncg;
-        hipLaunchKernelGGL(kern, dim3(std::min(items, MX_LONG_GRID)), dim3(64 * gpt), 0, s, J, J.rec, J.plist,
+        hipLaunchKernelGGL(kern, dim3(std::min(items, MX_LONG_GRID)), dim3(64 * gpt), lds, s, J, J.rec, J.plist,
                            J.ranges, J.attr, J.out, J.T_final, J.n_last, J.n_contrib, items, min_walk);
         return GS_OK;
     }
     auto kern = J.big ? k_blend_mx<1, true> : (J.nv > 1 ? k_blend_mx<MX_WIDE, false> : k_blend_mx<1, false>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(L.T * J.ncg), 1, z), dim3(64 * gpt), 0, s, J, J.rec, J.plist, J.ranges,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(L.T * J.ncg), 1, z), dim3(64 * gpt), lds, s, J, J.rec, J.plist, J.ranges,
                        J.attr, J.out, J.T_final, J.n_last, J.n_contrib);
     return GS_OK;
 }
@@ -1175,24 +1178,25 @@ gs_status launch_blend(const gs_attrs& a, const gs_params& p, const Layout& L, i
     J.lnp = L.T * ((L.tw * L.th) >> 6);
     J.lscale = lscale;
     dim3 grid(L.T, ncg, n_sets), block(L.tw * L.th);
+    const unsigned lds = (unsigned)(((L.tw * L.th) >> 6) * sizeof(BlendWave));
 #define ARGS J.rec, J.plist, J.ranges, J.attr, J.out, J.T_final, J.n_last, J.n_contrib
     void* tok;
     timing_begin(TK_BLEND, s, &tok);
     if (tgt) {
         switch (cg) {
-            case 1: hipLaunchKernelGGL((k_blend<1, true>), grid, block, 0, s, J, ARGS); break;
-            case 2: hipLaunchKernelGGL((k_blend<2, true>), grid, block, 0, s, J, ARGS); break;
-            case 4: hipLaunchKernelGGL((k_blend<4, true>), grid, block, 0, s, J, ARGS); break;
-            case 8: hipLaunchKernelGGL((k_blend<8, true>), grid, block, 0, s, J, ARGS); break;
-            case 16: hipLaunchKernelGGL((k_blend<16, true>), grid, block, 0, s, J, ARGS); break;
-            default: hipLaunchKernelGGL((k_blend<32, true>), grid, block, 0, s, J, ARGS); break;
+            case 1: hipLaunchKernelGGL((k_blend<1, true>), grid, block, lds, s, J, ARGS); break;
+            case 2: hipLaunchKernelGGL((k_blend<2, true>), grid, block, lds, s, J, ARGS); break;
+            case 4: hipLaunchKernelGGL((k_blend<4, true>), grid, block, lds, s, J, ARGS); break;
+            case 8: hipLaunchKernelGGL((k_blend<8, true>), grid, block, lds, s, J, ARGS); break;
+            case 16: hipLaunchKernelGGL((k_blend<16, true>), grid, block, lds, s, J, ARGS); break;
+            default: hipLaunchKernelGGL((k_blend<32, true>), grid, block, lds, s, J, ARGS); break;
         }
     } else {
         switch (cg) {
-            case 1: hipLaunchKernelGGL((k_blend<1, false>), grid, block, 0, s, J, ARGS); break;
-            case 2: hipLaunchKernelGGL((k_blend<2, false>), grid, block, 0, s, J, ARGS); break;
-            case 4: hipLaunchKernelGGL((k_blend<4, false>), grid, block, 0, s, J, ARGS); break;
-            default: hipLaunchKernelGGL((k_blend<8, false>), grid, block, 0, s, J, ARGS); break;
+            case 1: hipLaunchKernelGGL((k_blend<1, false>), grid, block, lds, s, J, ARGS); break;
+            case 2: hipLaunchKernelGGL((k_blend<2, false>), grid, block, lds, s, J, ARGS); break;
+            case 4: hipLaunchKernelGGL((k_blend<4, false>), grid, block, lds, s, J, ARGS); break;
+            default: hipLaunchKernelGGL((k_blend<8, false>), grid, block, lds, s, J, ARGS); break;
         }
     }
     timing_end(tok, s);
