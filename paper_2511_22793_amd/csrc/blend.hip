@@ -1206,12 +1206,12 @@ gs_status launch_blend(const gs_attrs& a, const gs_params& p, const Layout& L, i
 
 // the shared-geometry compositing over the groups whose walk (live-pass stop
 // positions) is longer than min_walk entries only
-void launch_blend_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out,
-                          int min_walk, hipStream_t s)
+gs_status launch_blend_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws,
+                               float* out, int min_walk, hipStream_t s)
 {
     BlendJob J = make_blend_job(a, p, L, n_sets, ws, out);
     J.across = 1;
-    launch_mx(J, L, s, min_walk);
+    return launch_mx(J, L, s, min_walk);
 }
 
 void launch_blend_persist(const BlendJob* jobs, int njobs, bool mx, uint32_t total, uint32_t* counter,

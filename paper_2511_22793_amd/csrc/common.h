@@ -221,8 +221,8 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
 // longer than min_walk entries only (the long-walk part of the fused
 // training pass); the per-pair geometric accumulators cleared before, and
 // folded per Gaussian after a backward (a forward's walk must be in place)
-void launch_blend_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws, float* out,
-                          int min_walk, hipStream_t s);
+gs_status launch_blend_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws,
+                               float* out, int min_walk, hipStream_t s);
 void launch_blend_bwd_sg_long(const gs_attrs& a, const gs_params& p, const Layout& L, int n_sets, char* ws,
                               const float* out, const float* target, const float* mean_grad, float scale,
                               const float* gscale, float* d_attr, int min_walk, float* lacc, hipStream_t s);

@@ -1177,7 +1177,7 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
         for (int i = 0; i < 3; ++i)
             if (hipStreamWaitEvent(ln->side[i], ln->fork, 0) != hipSuccess) return GS_ERR_HIP;
         // (first: it mostly finds no group and is gone before the classes fill the CUs)
-        launch_blend_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, TR_EMAX, ln->side[2]);
+        st = launch_blend_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, TR_EMAX, ln->side[2]);
         launch_blend_bwd_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, tt->target, mg, escale, tt->grad_scale,
                                  d_attr, TR_EMAX, llong, ln->side[2]);
         products(2, ln->side[0]);
@@ -1199,10 +1199,12 @@ gs_status gs_render_train(const gs_scene* scene, const gs_attrs* attrs, const gs
         hipLaunchKernelGGL(k_train_walk<128>, dim3(slots.walk[1]), dim3(256), 0, s, A, 1);
         hipLaunchKernelGGL(k_train_walk<64>, dim3(slots.walk[0]), dim3(256), 0, s, A, 0);
         timing_end(tok, s);
-        launch_blend_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, TR_EMAX, s);
+        st = launch_blend_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, TR_EMAX, s);
         launch_blend_bwd_sg_long(*attrs, *prm, L, n_sets, ws, spectrum, tt->target, mg, escale, tt->grad_scale,
                                  d_attr, TR_EMAX, llong, s);
     }
+    // (the side streams are joined by now)
+    if (st != GS_OK) return st;
     hipLaunchKernelGGL(k_train_loss_add, dim3(1), dim3(64), 0, s, lacc, llong, n_sets, lscale, tt->loss);
     if (!(flags & GS_TRAIN_DEFER_GEOMETRY)) {
         launch_geo_fold(L, ws, s);
