@@ -98,12 +98,14 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW
     const size_t HW = (size_t)J.H * J.W, pix = inside ? (size_t)row * J.W + col : 0;
     const int cs = J.C - 1;  // C is 1 or 2
     const size_t obase = (size_t)set * Fc * HW;
-    // CG = 16, 32, 64: the channel sums out[p][f] = sum_e w[p][e] v[e][f] of a
-    // run of 16 entries go to the FP32 matrix cores (v_mfma_f32_16x16x4_f32,
-    // A = the wave's pixel weights from LDS, B = the entries' attribute
-    // rows); the walk only produces the weights.  Smaller groups accumulate
-    // on the VALU, the values queued with the entries.
-    constexpr bool MF = CG == 16 || CG == 32 || CG == 64;
+    // CG = 16, 32 (the fused loss stage): the channel sums
+    // out[p][f] = sum_e w[p][e] v[e][f] of a run of 16 entries go to the FP32
+    // matrix cores (v_mfma_f32_16x16x4_f32, A = the wave's pixel weights from
+    // LDS, B = the entries' attribute rows); the walk only produces the
+    // weights.  Smaller groups accumulate on the VALU, the values queued with
+    // the entries.
+    constexpr bool MF = CG >= 16;
+    static_assert(!MF || FUSE, "more channel floats go to blend_mx_unit");
     constexpr int NB = MF ? CG / 16 : 1;
     constexpr int VG = MF ? 1 : CG;
     float acc[VG];
@@ -262,7 +264,7 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW
     auto loss_sum = [&](auto vc, float* x, int ch0, int slot) {
         constexpr int V = decltype(vc)::value;
         wave_reduce_scatter<V>(x, lane);
-        constexpr int sh = V >= 64 ? 0 : (V == 32 ? 1 : (V == 16 ? 2 : (V == 8 ? 3 : (V == 4 ? 4 : (V == 2 ? 5 : 6)))));
+        constexpr int sh = V == 16 ? 2 : (V == 8 ? 3 : (V == 4 ? 4 : (V == 2 ? 5 : 6)));
         const int ch = ch0 + (lane >> sh);
         if ((lane & ((1 << sh) - 1)) == 0 && ch < Fc) {
             J.lpart[(((size_t)set * Fc + ch) * 3 + slot) * J.lnp + (size_t)tile * (nthr >> 6) + wave] = x[0];
@@ -279,41 +281,32 @@ __device__ __forceinline__ void blend_tile_impl(const BlendJob& J, BlendWave* SW
 #pragma unroll
                 for (int r = 0; r < 4; ++r) tr[(16 * pb + 4 * (lane >> 4) + r) * 17 + (lane & 15)] = macc[pb][nb][r];
             wave_sync_lds();
-            if constexpr (fuse) {
-                // two 16-value arrays at a time next to the accumulators;
-                // the 16 target loads are issued before any store (the
-                // buffers are not known not to alias, so a store would
-                // order the loads after it)
-                const int ch0 = cg * CG + 16 * nb;
-                float x[16], y[16];
+            // two 16-value arrays at a time next to the accumulators; the 16
+            // target loads are issued before any store (the buffers are not
+            // known not to alias, so a store would order the loads after it)
+            const int ch0 = cg * CG + 16 * nb;
+            float x[16], y[16];
 #pragma unroll
-                for (int k = 0; k < 16; ++k)
-                    y[k] = inside && ch0 + k < Fc ? J.tgt[obase + spec_offset(ch0 + k, pix, cs, HW)] : 0.0f;
+            for (int k = 0; k < 16; ++k)
+                y[k] = inside && ch0 + k < Fc ? J.tgt[obase + spec_offset(ch0 + k, pix, cs, HW)] : 0.0f;
 #pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const size_t idx = obase + spec_offset(ch0 + k, pix, cs, HW);
-                    const float o = tr[lane * 17 + k];
-                    if (inside && ch0 + k < Fc) {
-                        ((GLOBAL_AS float*)out)[idx] = o;
-                        if (J.dpart) J.dpart[idx] = J.lscale * (o - y[k]);
-                    }
-                    x[k] = inside ? o : 0.0f;
+            for (int k = 0; k < 16; ++k) {
+                const size_t idx = obase + spec_offset(ch0 + k, pix, cs, HW);
+                const float o = tr[lane * 17 + k];
+                if (inside && ch0 + k < Fc) {
+                    ((GLOBAL_AS float*)out)[idx] = o;
+                    if (J.dpart) J.dpart[idx] = J.lscale * (o - y[k]);
                 }
-                loss_sum(std::integral_constant<int, 16>{}, x, ch0, 0);
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const float d = tr[lane * 17 + k] - y[k];
-                    x[k] = inside ? d * d : 0.0f;
-                }
-                loss_sum(std::integral_constant<int, 16>{}, x, ch0, 2);
-                loss_sum(std::integral_constant<int, 16>{}, y, ch0, 1);
-            } else if (inside) {
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const int ch = cg * CG + 16 * nb + k;
-                    if (ch < Fc) ((GLOBAL_AS float*)out)[obase + spec_offset(ch, pix, cs, HW)] = tr[lane * 17 + k];
-                }
+                x[k] = inside ? o : 0.0f;
             }
+            loss_sum(std::integral_constant<int, 16>{}, x, ch0, 0);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const float d = tr[lane * 17 + k] - y[k];
+                x[k] = inside ? d * d : 0.0f;
+            }
+            loss_sum(std::integral_constant<int, 16>{}, x, ch0, 2);
+            loss_sum(std::integral_constant<int, 16>{}, y, ch0, 1);
             wave_sync_lds();
         }
     } else {
@@ -1068,17 +1061,9 @@ BlendJob make_blend_job(const gs_attrs& a, const gs_params& p, const Layout& L, 
     return J;
 }
 
-// Channel floats per workgroup: the largest power of two that divides F*c,
-// at most 64, or the caller's choice (a power of two up to 64 dividing F*c).
-// (The backward and the persistent batch kernel cap it at 32.)
-int choose_chan_group(int Fc, int requested)
-{
-    if (requested > 0 && requested <= 64 && (requested & (requested - 1)) == 0 && Fc % requested == 0)
-        return requested;
-    int cg = 1;
-    while (cg < 64 && Fc % (cg * 2) == 0) cg *= 2;
-    return cg;
-}
+// Whether the caller's channel group is valid: a power of two up to 64 that
+// divides F*c.
+bool chan_group_valid(int Fc, int g) { return g > 0 && g <= 64 && (g & (g - 1)) == 0 && Fc % g == 0; }
 
 // Channel floats per workgroup of the compositing kernels: the caller's
 // choice where it is valid; else up to 8 channel floats go to k_blend in one
@@ -1090,7 +1075,7 @@ int choose_chan_group(int Fc, int requested)
 // 62 in one block of 16.
 int choose_blend_group(int Fc, int requested)
 {
-    if (requested > 0 && requested <= 64 && (requested & (requested - 1)) == 0 && Fc % requested == 0) return requested;
+    if (chan_group_valid(Fc, requested)) return requested;
     if (Fc > BLEND_ROW_CG) return (Fc + 15) / 16 * 16;
     int cg = 1;
     while (cg < Fc) cg *= 2;

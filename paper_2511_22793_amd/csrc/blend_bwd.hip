@@ -1097,10 +1097,9 @@ gs_status launch_blend_bwd(const gs_attrs& a, const gs_params& p, const Layout& 
     // the caller's group where it is valid; else the smallest
     // power of two that holds every channel float, 64 at most and the last
     // group partly filled: a walk per group costs more than empty channels
-    int cg = p.chan_group > 0 ? choose_chan_group(Fc, p.chan_group) : 1;
-    if (!(p.chan_group > 0 && cg == p.chan_group))
+    int cg = p.chan_group;
+    if (!chan_group_valid(Fc, cg))
         for (cg = 1; cg < 64 && cg < Fc;) cg *= 2;
-    if (cg > 64) cg = 64;
     const int ngr = (Fc + cg - 1) / cg;
     if (ngr > 65535) return GS_ERR_CAPACITY;
     const int shared = (L.nq == 1 && n_sets > 1) ? 1 : 0;

@@ -190,7 +190,7 @@ gs_status check_forward(const gs_scene* sc, const gs_attrs* a, const gs_queries*
                         const gs_params* p, const float* spectrum, const void* ws, size_t ws_bytes, Layout* L);
 void enqueue_prepare(const gs_scene* scene, const gs_queries* queries, const gs_grid* grid, const gs_params* prm,
                      const Layout& L, char* ws, hipStream_t s);
-int choose_chan_group(int Fc, int requested);
+bool chan_group_valid(int Fc, int g);
 int choose_blend_group(int Fc, int requested);
 struct BlendJob;
 void blend_mx_form(BlendJob* J, int64_t n);

@@ -757,7 +757,7 @@ gs_status gs_mlp_backward(const gs_mlp* net, const uint16_t* E, const float* mea
     gs_status e = check_rows(net, rows, mean, n);
     if (e != GS_OK) return e;
     if (!E || !d_attr || !st || !gr || !st->save_h1 || !st->save_h2 || !st->save_do || !st->save_dz2 ||
-        !st->save_dz1 || !st->genc || !st->dc || !st->wT || !st->partial || st->n_partial < 1)
+        !st->save_dz1 || !st->genc || !st->dc || !st->partial || st->n_partial < 1)
         return GS_ERR_INVALID_ARG;
     if (!gr->dW1 || !gr->db1 || !gr->dW2 || !gr->db2 || !gr->dW3 || !gr->db3 || !gr->dE) return GS_ERR_INVALID_ARG;
     const int NF = net->n_chan;

@@ -90,7 +90,6 @@ class State:
             self.dz2 = torch.empty(S, row_cap, HID, dtype=u16, device=dev)
             self.dz1 = torch.empty(S, row_cap, HID, dtype=u16, device=dev)
             self.dc = torch.empty(S, HID, device=dev)
-            self.wT = torch.empty(EMB * HID + HID * HID + HID * 2 * F, dtype=u16, device=dev)
             self.partial = torch.empty(n_partial, 2 * F * HID + HID * HID + HID * EMB, device=dev)
         self.n_partial = n_partial
 
@@ -100,7 +99,7 @@ class State:
         if self.training:
             s.save_h1, s.save_h2, s.save_do = _p(self.h1), _p(self.h2), _p(self.do)
             s.save_dz2, s.save_dz1, s.dc = _p(self.dz2), _p(self.dz1), _p(self.dc)
-            s.wT, s.partial, s.n_partial = _p(self.wT), _p(self.partial), self.n_partial
+            s.partial, s.n_partial = _p(self.partial), self.n_partial
         return s
 
 
