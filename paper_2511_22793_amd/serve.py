@@ -156,6 +156,16 @@ TILE_SHAPES = {256: ((16, 16), (8, 32), (32, 8)), 128: ((8, 16), (16, 8)), 64: (
 CHAN_GROUPS = (8, 16, 32)
 
 
+def group_candidates(fc: int) -> list:
+    """Channel groups to time for a job of fc channel floats: 0, the library's
+    own choice (every column of a set after one walk), and the groups dividing
+    fc (the walk repeated per group) that are not the same launch: up to 8
+    channel floats the library takes the smallest power of two that holds
+    them."""
+    own = 1 << (fc - 1).bit_length() if fc <= 8 else 0
+    return [0] + [c for c in [c for c in CHAN_GROUPS if fc % c == 0] or [min(fc & -fc, 32)] if c != own]
+
+
 def _time(fn, reps: int) -> float:
     """Median ms of fn() over reps runs (HIP events on the current stream)."""
     fn()
@@ -176,8 +186,7 @@ class Autotuner:
     persistent workgroups.
 
     Per job signature (Gaussian count, grid, channels): every candidate
-    shape of each class, with the library's own channel grouping and every
-    group dividing F*c, is timed on the
+    shape of each class, with each of group_candidates(F*c), is timed on the
     job's first `probe` receivers as a one-job batch; the best per class is
     kept (cached in `cache`, a JSON file when `path` is given).  The class
     whose summed best times over the batch is smallest wins, then the
@@ -203,10 +212,7 @@ class Autotuner:
         if key in self.cache:
             return self.cache[key]
         probe = job.head(self.probe)
-        fc = job.F * (2 if job.is_complex else 1)
-        # 0: the library's own choice (every column of a set after one walk);
-        # with a group the walk is repeated per group
-        groups = [0] + ([c for c in CHAN_GROUPS if fc % c == 0] or [fc & -fc if fc & -fc <= 32 else 32])
+        groups = group_candidates(job.F * (2 if job.is_complex else 1))
         res = {}
         for block, shapes in TILE_SHAPES.items():
             best = None
