@@ -104,10 +104,13 @@ typedef struct {
     int32_t atten_ref; /* d measured to: 0 the receiver, 1 the transmitter (0) */
     float margin;      /* support-rectangle margin, px (1e-3) */
     int64_t pair_capacity; /* (Gaussian, tile) pairs per query; 0 = n * min(tiles, 64) + 4096 */
-    int32_t chan_group;    /* channel floats per blend workgroup (a power of two dividing F*c, at most
-                              64; the per-group backward and batched blends use at most 32; the
-                              shared-geometry backward takes all columns at once), 0 = automatic:
-                              the largest such power of two */
+    int32_t chan_group;    /* channel floats per workgroup of the compositing and of the per-group
+                              backward, each walking the lists again (a power of two up to 64
+                              that divides F*c; anything else counts as 0); the forms over shared
+                              geometry take all columns at once.  0 = automatic: all channel
+                              floats of a set after one walk (compositing); the smallest power of
+                              two that holds them, at most 64, the last group partly filled
+                              (per-group backward) */
     int32_t options;       /* GS_OPT_* bits (0) */
 } gs_params;
 
@@ -121,10 +124,12 @@ typedef struct {
  * geometry once for all sets and channels; both give the same gradients up
  * to summation order).  For comparisons and tests. */
 #define GS_OPT_BWD_PER_GROUP 2
-/* options: gs_render_blend() takes the per-set, per-channel-group kernel
- * even where the sets share one geometry (the default there walks each
- * pixel once for all sets and forms the channel sums on the matrix cores;
- * the spectra agree to FP32 summation order).  For comparisons and tests. */
+/* options: gs_render_blend() walks for every set apart even where the sets
+ * share one geometry (the default there walks each pixel once for all sets):
+ * with a chan_group of at most 8 in the row form, which adds on the vector
+ * units, else in the matrix-core form, set by set.  Every form adds a pixel's
+ * entries in list order as one chain of fused multiply-adds, so the spectra
+ * are the same bits.  For comparisons and tests. */
 #define GS_OPT_BLEND_PER_GROUP 4
 
 /* Per-query device-side results, read with gs_read_flags(). */
@@ -464,7 +469,8 @@ typedef struct {
  * i < count[count_stride ? s : 0] (device count, so the list can come from a
  * device-side pass).  row_cap: rows per set the saved-activation buffers
  * hold (>= every count).  grid_x: workgroups per set, each taking 64 rows
- * per round (0 = 32). */
+ * per round (0 = automatic: about two rounds of what fits the device, no more
+ * than row_cap needs). */
 typedef struct {
     int32_t n_sets;
     const float* tx;        /* [S][3] */
@@ -682,8 +688,9 @@ gs_status gs_screen_radius(const void* workspace, size_t ws_bytes, int32_t n, in
  * library (each job to the stream with the least Gaussians x queries so far;
  * forked from and joined back into the caller's stream with events, so a
  * graph capture records them as parallel branches), then one persistent
- * blend kernel whose workgroups pull (job, query, channel group, tile) items
- * from a device counter in job order, so the job order is the service order.
+ * blend kernel whose workgroups take (job, query, channel group, tile) items
+ * in job order (three quarters dealt out in turn, the rest from a device
+ * counter), so the job order is the service order.
  * Spectra and workspace state are those that gs_render_forward() leaves for
  * the same job, bit for bit.
  *

@@ -1083,9 +1083,11 @@ int choose_blend_group(int Fc, int requested)
 }
 
 // Column ranges of the matrix-core kernel over `nb` column blocks: enough
-// waves to fill the chip several times over (12 are resident per CU), at
-// least MX_MIN_BLOCKS 16-column blocks after each walk, and a multiple of the
-// 8 XCDs where there are that many.
+// waves to fill the chip several times over (8 are resident per CU, by 240
+// registers and by 20 KB of LDS a wave: 2048 on the chip; 8192 waves took 369
+// us at 64 sets of 128 columns, 16384 349, 24576 406), at least MX_MIN_BLOCKS
+// 16-column blocks after each walk, and a multiple of the 8 XCDs where there
+// are that many.
 constexpr int MX_WAVES = 16384, MX_MIN_BLOCKS = 4;
 static int mx_split(int64_t groups, int nb, int nv)
 {

@@ -37,7 +37,7 @@ class Params:
     chan_group: int = 0
     forward_only: bool = False
     bwd_per_group: bool = False  # backward per set and channel group even over shared geometry
-    blend_per_group: bool = False  # compositing per set and channel group even over shared geometry
+    blend_per_group: bool = False  # compositing per set even over shared geometry
 
     def c(self) -> GsParams:
         return GsParams(self.alpha_min, self.alpha_max, self.T_min, self.dilation, self.r_near, self.atten_power,
